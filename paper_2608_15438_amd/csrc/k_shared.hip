@@ -17,7 +17,7 @@
 //          counts) form the scan list in cluster order with their pair and
 //          work ranges (rows x groups of <= g queries); the pairs are then
 //          scattered by cluster;
-//  scan    persistent waves take tiles of SHARED_TILE work from an atomic
+//  scan    persistent waves take tiles of the work space from an atomic
 //          counter and gather consecutive units of the tile into batches
 //          whose query rows sit in LDS.  Each row's head (its first
 //          scan_head bytes) is read once for all queries of its unit and
@@ -39,7 +39,13 @@
 #define NR_SHARED_BLOCKS_PER_CU 8
 #endif
 #ifndef NR_SHARED_TILE
-#define NR_SHARED_TILE 4096     // work (rows x query groups) per scan tile
+#define NR_SHARED_TILE 4096     // work (rows x query groups) per scan tile, at most
+#endif
+#ifndef NR_SHARED_TILE_MIN
+#define NR_SHARED_TILE_MIN 256  // and at least
+#endif
+#ifndef NR_SHARED_TPW
+#define NR_SHARED_TPW 4         // tiles per wave that a smaller tile aims at
 #endif
 #ifndef NR_SCAN_U1
 #define NR_SCAN_U1 6            // head loads in flight per lane (16-byte heads)
@@ -62,7 +68,19 @@
 
 namespace nr {
 
-constexpr uint64_t SHARED_TILE = NR_SHARED_TILE;
+// Work per scan tile.  A wave's time on a tile is a chain of dependent loads
+// (list, pairs, query rows, heads, rows), so the scan ends with its slowest
+// waves: at a fixed 4096, 2,000 queries of 1536-d rows (0.75M work) filled 250
+// of 8192 waves.  Large scans keep 4096; smaller ones are cut so that each
+// wave gets NR_SHARED_TPW tiles, down to NR_SHARED_TILE_MIN, below which a
+// tile holds few whole batches.  Whole searches on MI355X: 500k x 1536 fp32,
+// 2,000 queries 3.85 -> 1.63 ms; 25M x 96 fp32, 10,000 queries 5.70 -> 4.89
+// ms; 256M x 128 uint8 (tile 4096 either way) 5.04 ms; a minimum of 64, or 2
+// or 8 tiles per wave, within 3 % of this
+__device__ __forceinline__ uint64_t shared_tile(uint64_t work, uint32_t waves) {
+  const uint64_t t = work / ((uint64_t)waves * NR_SHARED_TPW);
+  return t > NR_SHARED_TILE ? NR_SHARED_TILE : (t < NR_SHARED_TILE_MIN ? NR_SHARED_TILE_MIN : t);
+}
 
 typedef unsigned int su32x4 __attribute__((ext_vector_type(4)));
 
@@ -414,7 +432,7 @@ __device__ __forceinline__ void add_survivor(const SharedArgs &a, uint32_t q, ui
 // ------------------------------------------------------------------ scan
 // The work of scan-list entry i (cluster slist[i]) is swork[i] = rows x query
 // groups; a unit (group gi, row chunk ch) starts at swork_off[i] + gi * rows +
-// ch * R.  A tile is a SHARED_TILE-long range of that work space and takes the
+// ch * R.  A tile is a range of that work space (shared_tile long) and takes the
 // units that start inside it, so each unit belongs to exactly one tile.  A
 // wave gathers up to SCAN_UMAX consecutive units of its tile (with up to 32
 // query slots for 128-byte rows, fewer for longer ones) into a batch whose
@@ -537,7 +555,8 @@ __global__ void __launch_bounds__(256, NSEG <= 1 ? NR_SCAN_WAVES1 : (NSEG > 8 ? 
   uint32_t *olk = s_ok[w];
   const int64_t NS = (int64_t)a.lmeta[0];
   const uint64_t W = a.lmeta[2];
-  const uint64_t ntiles = (W + SHARED_TILE - 1) / SHARED_TILE;
+  const uint64_t tile = shared_tile(W, gridDim.x * (256 / WAVE));
+  const uint64_t ntiles = (W + tile - 1) / tile;
   const int rb = a.row_bytes;
   const int k = a.k;
   const unsigned char *queries = (const unsigned char *)a.queries;
@@ -551,8 +570,8 @@ __global__ void __launch_bounds__(256, NSEG <= 1 ? NR_SCAN_WAVES1 : (NSEG > 8 ? 
     if (lane == 0) t = atomicAdd(a.counter, 1ull);
     t = bcast_u64(t, 0);
     if (t >= ntiles) break;
-    const uint64_t ws = (uint64_t)t * SHARED_TILE;
-    const uint64_t we = ws + SHARED_TILE < W ? ws + SHARED_TILE : W;
+    const uint64_t ws = (uint64_t)t * tile;
+    const uint64_t we = ws + tile < W ? ws + tile : W;
     // the list entry holding ws: the last i with swork_off[i] <= ws (64-ary search)
     int64_t lo = 0, hi = NS;
     while (hi - lo > 1) {

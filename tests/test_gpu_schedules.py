@@ -1,0 +1,85 @@
+"""The batch-shared schedule against the per-query one (same lists, bit for
+bit) over scans of small, middling and large work, the three cases of the
+scan's tile size, and over neighbours per query up to the largest k."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+pytestmark = pytest.mark.gpu
+
+
+def make_index(n, d, b, dtype, head, seed=0):
+    """Random rows in random buckets, one cluster per non-empty bucket; the
+    latents are d -> b random projections."""
+    from paper_2608_15438_amd import neuroute as NR
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    rng = np.random.default_rng(seed)
+    if dtype == NR.NR_U8:
+        rows = torch.randint(0, 256, (n, d), generator=g, device="cuda", dtype=torch.uint8)
+    else:
+        rows = torch.randn((n, d), generator=g, device="cuda")
+    sizes = np.bincount(rng.integers(0, 1 << b, n), minlength=1 << b)
+    nz = sizes[sizes > 0]
+    bc = np.concatenate([[0], np.cumsum(sizes > 0)])
+    cl = np.concatenate([[0], np.cumsum(nz)])
+    raw = rows.view(torch.uint8)
+    pay = torch.cat([raw[:, :head].reshape(-1), raw.reshape(-1)]) if head else raw.reshape(-1)
+    W = (rng.standard_normal((b, d)) / np.sqrt(d)).astype(np.float32)
+    scale = 1 / 255 if dtype == NR.NR_U8 else 1.0
+    tau = np.zeros(b, np.float32)
+    ix = NR.Index(n=n, d=d, dtype=dtype, b=b, weights=[W], biases=[np.zeros(b, np.float32)],
+                  input_scale=scale, tau=tau, rows=pay.contiguous(),
+                  row_ids=torch.randperm(n, generator=g, device="cuda"),
+                  bc_off=torch.from_numpy(bc.astype(np.int32)).cuda(),
+                  cl_off=torch.from_numpy(cl.astype(np.int64)).cuda(),
+                  centroids=torch.randn((len(nz), b), generator=g, device="cuda"),
+                  head_bytes=head, head_copy=int(head > 0))
+    return ix, rows
+
+
+def both(ix, q, k, P, b, **kw):
+    from paper_2608_15438_amd import neuroute as NR
+    r = [ix.nr_search(q, k, P, NR.Params(l_sel=b, r_max=b, k_c=64, refine_mode=m, **kw))
+         for m in (NR.NR_REFINE_PER_QUERY, NR.NR_REFINE_SHARED)]
+    assert torch.equal(r[0][0], r[1][0])
+    assert torch.equal(r[0][1], r[1][1])
+    return r[1]
+
+
+@pytest.mark.parametrize("dtype,d,head", [("u8", 16, 0), ("u8", 128, 16), ("f32", 24, 64),
+                                          ("f32", 260, 0)])
+@pytest.mark.parametrize("n,b,nq,P,seed_rows", [
+    (500, 3, 70, 8, 64),          # less work than one smallest tile per wave
+    (60_001, 8, 2049, 256, 64),   # tiles between the smallest and the largest
+    (60_001, 8, 300, 100, 0),     # the default seed
+])
+def test_shared_equals_per_query(dtype, d, head, n, b, nq, P, seed_rows):
+    from paper_2608_15438_amd import neuroute as NR
+    dt = NR.NR_U8 if dtype == "u8" else NR.NR_F32
+    ix, rows = make_index(n, d, b, dt, head)
+    g = torch.Generator(device="cuda").manual_seed(1)
+    at = torch.randint(0, n, (nq,), generator=g, device="cuda")
+    q = rows[at].clone()
+    for k in (1, 10, 64):
+        ids, dists = both(ix, q, k, P, b, shared_seed_rows=seed_rows)
+        if k == 10:   # against plain distances to the rows listed
+            pos = torch.empty(n, dtype=torch.int64, device="cuda")
+            pos[ix.dev[1]] = torch.arange(n, device="cuda")
+            ok = ids >= 0
+            x = rows[pos[ids.clamp_min(0)]].double()
+            want = ((x - q[:, None].double()) ** 2).sum(-1)
+            # fp32 sums of d squares: relative error at most d roundings
+            assert ((want - dists.double()).abs() <= d * 2.0 ** -23 * want + 1e-30)[ok].all()
+    ix.close()
+
+
+def test_shared_equals_per_query_large_scan():
+    # more work (rows x groups of 8 queries) than 4 tiles of 4096 per wave
+    from paper_2608_15438_amd import neuroute as NR
+    ix, rows = make_index(150_000, 16, 8, NR.NR_U8, 0)
+    g = torch.Generator(device="cuda").manual_seed(1)
+    q = rows[torch.randint(0, 150_000, (8192,), generator=g, device="cuda")].clone()
+    both(ix, q, 10, 256, 8, shared_seed_rows=256)
+    ix.close()
+
