@@ -145,8 +145,8 @@ typedef struct {
   int32_t lowq_or;
   int32_t refine_mode;   /* NR_REFINE_AUTO / _PER_QUERY / _SHARED (same results) */
   int32_t shared_seed_rows; /* shared schedule: rows of each list's leading clusters
-                               kept for the query's own pass (>= k); 0: 4096, or
-                               1024 for rows longer than 1024 bytes */
+                               kept for the query's own pass (>= k); 0: chosen
+                               per query from its list's rows and k */
   int32_t m_knots;
   float m_x[NR_MAX_KNOTS];
   float m_y[NR_MAX_KNOTS];

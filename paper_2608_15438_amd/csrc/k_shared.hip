@@ -5,7 +5,7 @@
 //
 //  hist    per query (one wave, at the end of the route kernel once the
 //          query's list is final): the leading clusters of its list that
-//          cover at least seed_min rows stay with the query; every later
+//          cover at least the seed's rows stay with the query; every later
 //          (cluster, query) pair is counted per cluster; |q|^2 and its head
 //          part are kept for uint8 rows;
 //  seed    the per-query kernels refine each query's leading clusters.  Their
@@ -142,7 +142,7 @@ PairHistArgs pair_hist_args(const SharedArgs &a) {
   h.hist = a.hist;
   h.cl_off = a.cl_off;
   h.n_clusters = a.n_clusters;
-  h.seed_min = a.seed_min;
+  h.seed = a.seed;
   h.cseed = a.cseed;
   h.rfull = a.rfull;
   h.qnorm = a.qnorm;

@@ -612,9 +612,11 @@ nr::SharedArgs shared_args(const nr_index *ix, const nr_params *p, const void *q
   a.scan_head = scan_head(ix);
   a.scan_hb = (const unsigned char *)ix->d.rows;  // the head plane, or the rows themselves
   a.scan_hs = ix->d.head_bytes > 0 ? (uint64_t)ix->d.head_bytes : (uint64_t)a.row_bytes;
-  const uint32_t seed = p->shared_seed_rows > 0 ? (uint32_t)p->shared_seed_rows
-                        : (a.row_bytes > 1024 ? nr::SEED_ROWS_LONG : nr::SEED_ROWS);
-  a.seed_min = seed > (uint32_t)k ? seed : (uint32_t)k;
+  a.seed = nr::seed_rule(a.is_u8, a.row_bytes, k);
+  if (p->shared_seed_rows > 0) {
+    a.seed.lo = p->shared_seed_rows > k ? (uint32_t)p->shared_seed_rows : (uint32_t)k;
+    a.seed.div = a.seed.brief = 0;
+  }
   a.n_clusters = ix->d.n_clusters;
   a.ra = row_addr(ix);
   a.row_ids = ix->d.row_ids;

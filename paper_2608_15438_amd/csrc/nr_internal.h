@@ -24,12 +24,38 @@ constexpr int64_t QUERY_CHUNK = 16384;    // queries per internal launch sequenc
 #define NR_OWN_TILE_MIN_ROWS 2048
 #endif
 constexpr uint32_t OWN_TILE_MIN_ROWS = NR_OWN_TILE_MIN_ROWS;  // smallest tile of the own pass
-#ifndef NR_SEED_ROWS
-#define NR_SEED_ROWS 4096
-#endif
-constexpr uint32_t SEED_ROWS = NR_SEED_ROWS;      // rows of a query's first clusters refined on their own
-constexpr uint32_t SEED_ROWS_LONG = 1024;          // the same for rows past 1 KB, which the scan
-                                                   // mostly settles after their first 1 KB
+// Rows of a query's first clusters that it refines on its own before the
+// shared scan: about 1 / div of the rows its list holds (estimated from the
+// list's first clusters, which are its larger ones), within [lo, hi]; lists
+// estimated at most `brief` rows long take 2 lo, so that a batch of short
+// lists leaves the scan nothing (1M x 128, 725 rows a list: 0.78 ms, but 0.95
+// ms with the few lists past 1024 rows in the scan).  More seed rows give tighter bounds
+// (fewer survivors of the scan, and for uint8 rows fewer rows that pass the
+// head test) but are read once per query instead of once per batch, and the
+// rows that the bound acts on grow with the list.  fp32 heads drop few rows,
+// so fp32 seeds are the smaller; uint8 rows past 1 KB keep 1024.  The bound is
+// the seed's k-th key, so a large k needs SEED_ROWS_PER_K rows per neighbour:
+// with 8, the survivors of k = 64 flooded their lists.  Whole searches on
+// MI355X with seeds of 256 / 512 / 1024 / 2048 / 4096 rows, ms:
+//   fp32, k = 10:   25M x 96 (11k rows a list) 3.62 / 3.51 / 3.65 / 4.2 / 4.89, 1M x 200 (9k)
+//                   2.07 / 2.15 / 2.39 / 2.98 / 4.10, 500k x 768 (9k) 14.8 / 3.26 / 3.00 /
+//                   3.68 / 5.46, 500k x 1536 (4k) 1.16 / 1.27 / 1.63 / - / -
+//   uint8, k = 10:  4M x 256 (14k) 1.56 / 1.47 / 1.46 / 1.62 / 1.92, 32M x 128 (23k) 5.41 /
+//                   3.16 / 2.86 / 2.97 / 3.12, 256M x 128 (56k) 8.5 / 6.3 / 5.5 / 5.17 / 5.04
+//   k = 64:         1M x 100 fp32 2.91 / 2.01 / 1.96 / 2.15 / 2.65, 4M x 256 uint8 7.85 /
+//                   2.63 / 1.82 / 1.88 / 2.15, 500k x 1536 fp32 20 / 18 / 4.75 / 4.29 / 5.89
+struct SeedRule {
+  uint32_t lo, hi, div, brief;  // div 0: lo rows whatever the list
+};
+constexpr uint32_t SEED_ROWS_PER_K = 32;
+inline SeedRule seed_rule(bool is_u8, int row_bytes, int k) {
+  SeedRule r = is_u8 ? (row_bytes > 1024 ? SeedRule{1024, 1024, 0, 0} : SeedRule{1024, 4096, 12, 8192})
+                     : SeedRule{512, 4096, 24, 2048};
+  const uint32_t by_k = SEED_ROWS_PER_K * (uint32_t)k;
+  if (r.lo < by_k) r.lo = by_k;
+  if (r.hi < r.lo) r.hi = r.lo;
+  return r;
+}
 #ifndef NR_SURVIVOR_CAP
 #define NR_SURVIVOR_CAP 2048
 #endif
@@ -131,7 +157,7 @@ struct PairHistArgs {
   uint32_t *hist;               // [n_clusters + 1] pairs per cluster past the leading clusters
   const uint64_t *cl_off;
   int64_t n_clusters;
-  uint32_t seed_min;            // rows the leading clusters cover at least
+  SeedRule seed;                // rows the leading clusters cover at least
   int32_t *cseed;               // [nq] leading clusters
   uint32_t *rfull;              // [nq] rows of the leading clusters (whole list: eager_rows)
   uint2 *qnorm;                 // [nq] uint8 rows: |q|^2 and its head part
@@ -231,7 +257,7 @@ struct SharedArgs {
   int64_t nq;
   int k, is_u8, row_bytes;
   int g;                      // queries per work unit (SHARED_G)
-  uint32_t seed_min;          // rows the leading clusters of a list cover at least
+  SeedRule seed;              // rows the leading clusters of a list cover at least
   int64_t n_clusters;
   RowAddr ra;                 // permuted payload
   int scan_head;              // bytes of each row the scan's filter reads (its head)
@@ -482,7 +508,7 @@ __device__ __forceinline__ int lower_bound_u64(const uint64_t *a, int n, uint64_
 }
 
 // One wave, query q with list cl[0..n): the leading clusters covering at
-// least seed_min rows stay with the query (cseed[q]); every later (cluster,
+// least the seed's rows stay with the query (cseed[q]); every later (cluster,
 // query) pair is counted in hist (its rank among the cluster's pairs goes to
 // pair_rank); rfull[q] gets the rows of the leading
 // clusters (of the whole list with eager_rows); for uint8 rows qnorm[q] gets
@@ -494,7 +520,8 @@ __device__ inline void pair_hist_wave(const PairHistArgs &h, int64_t q, const ui
   const bool all = h.eager_rows != 0;
   uint64_t run = 0;
   int cs = -1;
-  // the seed: sizes of the leading clusters until they cover seed_min rows
+  // the seed: sizes of the leading clusters until they cover its rows
+  uint32_t seed_min = 0;
   for (int i0 = 0; i0 < n && (cs < 0 || all); i0 += WAVE) {
     const int i = i0 + lane;
     uint64_t sz = 0;
@@ -503,9 +530,16 @@ __device__ inline void pair_hist_wave(const PairHistArgs &h, int64_t q, const ui
       if (c < h.n_clusters) sz = h.cl_off[(uint64_t)c + 1] - h.cl_off[c];
     }
     const uint64_t incl = wave_incl_scan_u64(sz);
+    if (i0 == 0) {
+      // the list's rows, from the mean size of its first clusters
+      const uint64_t est = bcast_u64(incl, WAVE - 1) * (uint64_t)n / (uint64_t)(n < WAVE ? n : WAVE);
+      const uint64_t want = h.seed.div > 0 ? est / h.seed.div : 0;
+      seed_min = want > h.seed.hi ? h.seed.hi : (want < h.seed.lo ? h.seed.lo : (uint32_t)want);
+      if (est <= h.seed.brief) seed_min = 2 * h.seed.lo;
+    }
     int upto = WAVE - 1;
     if (cs < 0) {
-      const uint64_t hit = ballot(i < n && run + incl >= h.seed_min);
+      const uint64_t hit = ballot(i < n && run + incl >= seed_min);
       if (hit) {
         cs = i0 + __ffsll((unsigned long long)hit);  // first position past the seed
         if (!all) upto = cs - 1 - i0;
