@@ -2,14 +2,15 @@
 // "In-bucket clustering"; binarisation thresholds, Sec. 3.2.3), from the
 // latents the encoder kernel gives the base rows:
 //   tau      per latent dimension, the lower median of a sample of rows
-//            (radix select on order-preserving keys, one block per dimension);
+//            (radix select on order-preserving keys);
 //   codes    bit j of a row's code = [l_j >= tau_j] (Eq. 10) and the bucket
 //            sizes (atomic counts);
 //   buckets  exclusive scan of the sizes, an atomic scatter of the row ids into
 //            bucket order, then every bucket's ids sorted ascending;
-//   k-means  one block per bucket with K_B >= 2 clusters: k-means++ on a
-//            sample, then Lloyd passes over the whole bucket, in fp64 and in a
-//            fixed order of summation (below);
+//   k-means  of the buckets with K_B >= 2 clusters: k-means++ on a sample (a
+//            wave per small bucket, a block per larger one), then Lloyd passes
+//            over the whole bucket (a wave per 64 members, then a wave per
+//            cluster), in fp64 and in a fixed order of summation (below);
 //   layout   clusters kept per bucket -> bc_off (scan), every bucket's rows in
 //            (cluster, id) order -> row_ids, cluster sizes -> cl_off (scan),
 //            centroids = fp64 means of the member latents (in id order),
@@ -31,6 +32,7 @@ constexpr int BT = 256;               // threads per block of the build kernels
 constexpr int SCAN_PER_THREAD = 16;   // items per thread of the scans
 constexpr int64_t SCAN_BLOCK = (int64_t)BT * SCAN_PER_THREAD;
 constexpr int SORT_LDS = 4096;        // keys sorted in LDS by one block
+constexpr int64_t TAU_SMALL = 8192;   // sample rows from which the whole chip selects tau
 
 // ------------------------------------------------------------------ helpers
 __device__ __forceinline__ uint32_t mix32_dev(uint64_t x, uint32_t seed) {
@@ -40,17 +42,6 @@ __device__ __forceinline__ uint32_t mix32_dev(uint64_t x, uint32_t seed) {
   return (uint32_t)((h >> 16) ^ h);
 }
 
-// fp64 squared distance of an fp32 latent row to an fp64 point, dimensions
-// added in order (no contraction: the build compiles with -ffp-contract=off)
-__device__ __forceinline__ double sqd_row(const float *x, const double *c, int b) {
-  double acc = 0.0;
-  for (int j = 0; j < b; ++j) {
-    const double t = (double)x[j] - c[j];
-    acc = acc + t * t;
-  }
-  return acc;
-}
-
 __device__ __forceinline__ int64_t d2_weight(double d2) {
   double w = floor(d2 * 1048576.0);           // 2^20
   if (w > 1073741824.0) w = 1073741824.0;     // 2^30
@@ -58,8 +49,8 @@ __device__ __forceinline__ int64_t d2_weight(double d2) {
 }
 
 // block-wide exclusive scan of one value per thread (any integral T);
-// *total gets the block's sum.  Uses `sh` (BT / WAVE entries).
-template <class T>
+// *total gets the block's sum.  Uses `sh` (NT / WAVE entries).
+template <class T, int NT = BT>
 __device__ __forceinline__ T block_excl_scan(T v, T *sh, T *total) {
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   T incl = v;
@@ -71,7 +62,7 @@ __device__ __forceinline__ T block_excl_scan(T v, T *sh, T *total) {
   if (lane == WAVE - 1) sh[w] = incl;
   __syncthreads();
   T before = 0, all = 0;
-  for (int i = 0; i < BT / WAVE; ++i) {
+  for (int i = 0; i < NT / WAVE; ++i) {
     if (i < w) before += sh[i];
     all += sh[i];
   }
@@ -139,6 +130,8 @@ hipError_t launch_scan(const In *in, int64_t n, Out *out, uint64_t *blk, hipStre
   return hipGetLastError();
 }
 
+int build_pad(int b) { return (b + 3) / 4 * 4; }
+
 size_t build_scan_blocks(int64_t n) { return (size_t)((n + SCAN_BLOCK - 1) / SCAN_BLOCK) + 2; }
 
 // ------------------------------------------------------------------ tau
@@ -150,6 +143,69 @@ __device__ __forceinline__ uint32_t fkey(float f) {
 }
 __device__ __forceinline__ float fkey_inv(uint32_t k) {
   return __uint_as_float((k & 0x80000000u) ? (k & 0x7FFFFFFFu) : ~k);
+}
+
+// Radix select of every dimension's (ns - 1) / 2-th smallest value at once:
+// per digit (8 bits, from the top) one pass over the sample counts, in LDS, the
+// digits of the keys that match the dimension's prefix so far, and one block
+// per dimension picks the digit holding the rank.  Rows are read whole and in
+// order by the whole chip: 1M x 16 latents take 0.14 ms where one block per
+// dimension (k_build_tau below) read its column in 5.6 ms.
+struct TauState {
+  uint32_t prefix, rank;
+};
+
+// thread t counts dimension t % b; a step of the block reads 256 / b rows
+__global__ void __launch_bounds__(BT) k_tau_hist(const float *lg, int64_t ns, int b, int shift,
+                                                 const TauState *st, uint32_t *hist) {
+  extern __shared__ uint32_t h[];  // [b][256]
+  for (int i = threadIdx.x; i < b * 256; i += BT) h[i] = 0;
+  __syncthreads();
+  const int rows = BT / b;
+  if ((int)threadIdx.x < rows * b) {
+    const int j = threadIdx.x % b;
+    const uint32_t prefix = st[j].prefix;
+    const uint32_t mask = shift == 24 ? 0u : (0xFFFFFFFFu << (shift + 8));
+    const int64_t total = ns * b, step = (int64_t)gridDim.x * rows * b;
+    for (int64_t e = (int64_t)blockIdx.x * rows * b + threadIdx.x; e < total; e += 4 * step) {
+      float v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = e + u * step < total ? lg[e + u * step] : 0.0f;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const uint32_t k = fkey(v[u]);
+        if (e + u * step < total && (k & mask) == prefix)
+          atomicAdd(&h[j * 256 + ((k >> shift) & 255u)], 1u);
+      }
+    }
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < b * 256; i += BT)
+    if (h[i]) atomicAdd(&hist[i], h[i]);
+}
+
+// the digit of dimension blockIdx.x: the last whose count of keys below it is
+// at most the rank; clears the counts for the next pass
+__global__ void __launch_bounds__(256) k_tau_pick(uint32_t *hist, TauState *st, int shift,
+                                                  float *tau) {
+  __shared__ uint32_t sh[BT / WAVE];
+  const int j = blockIdx.x, d = threadIdx.x;
+  const TauState s = st[j];
+  const uint32_t c = hist[j * 256 + d];
+  hist[j * 256 + d] = 0;
+  uint32_t tot;
+  const uint32_t below = block_excl_scan<uint32_t>(c, sh, &tot);
+  if (below <= s.rank && s.rank < below + c) {   // one digit: the rank is below tot
+    const uint32_t p = s.prefix | ((uint32_t)d << shift);
+    st[j] = TauState{p, s.rank - below};
+    if (shift == 0) tau[j] = fkey_inv(p);
+  }
+}
+
+__global__ void k_tau_init(TauState *st, uint32_t *hist, int b, uint32_t rank) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < b) st[i] = TauState{0u, rank};
+  if (i < b * 256) hist[i] = 0;
 }
 
 // one block per dimension: the (ns - 1) / 2-th smallest value of column j
@@ -232,22 +288,21 @@ __global__ void k_build_scatter(const uint32_t *codes, int64_t n, const uint64_t
   }
 }
 
-// Ascending sort of keys[0, n) by one block: bitonic in LDS for n <= SORT_LDS,
-// else a stable LSD radix sort over 4-bit digits through tmp[0, n).
-template <class K>
-__device__ void block_sort(K *keys, int64_t n, K *tmp, int key_bits) {
-  __shared__ K lds[SORT_LDS];
-  __shared__ uint32_t cnt[16][BT];
-  __shared__ uint32_t shs[BT / WAVE];
+// Ascending sort of keys[0, n) by one block of NT threads: bitonic in LDS for
+// n <= SORT_LDS (`lds`, SORT_LDS keys), else a stable LSD radix sort over 4-bit
+// digits through tmp[0, n) (`cnt`, 16 x NT counts).
+template <int NT, class K>
+__device__ void block_sort(K *keys, int64_t n, K *tmp, int key_bits, K *lds, uint32_t *cnt,
+                           uint32_t *shs) {
   if (n <= 1) return;
   if (n <= SORT_LDS) {
     int p2 = 1;
     while (p2 < n) p2 <<= 1;
-    for (int i = threadIdx.x; i < p2; i += BT) lds[i] = i < n ? keys[i] : (K)~(K)0;
+    for (int i = threadIdx.x; i < p2; i += NT) lds[i] = i < n ? keys[i] : (K)~(K)0;
     __syncthreads();
     for (int k = 2; k <= p2; k <<= 1)
       for (int jj = k >> 1; jj > 0; jj >>= 1) {
-        for (int i = threadIdx.x; i < p2; i += BT) {
+        for (int i = threadIdx.x; i < p2; i += NT) {
           const int l = i ^ jj;
           if (l > i) {
             const K a = lds[i], c = lds[l];
@@ -260,36 +315,36 @@ __device__ void block_sort(K *keys, int64_t n, K *tmp, int key_bits) {
         }
         __syncthreads();
       }
-    for (int i = threadIdx.x; i < n; i += BT) keys[i] = lds[i];
+    for (int i = threadIdx.x; i < n; i += NT) keys[i] = lds[i];
     __syncthreads();
     return;
   }
-  const int64_t per = (n + BT - 1) / BT;
+  const int64_t per = (n + NT - 1) / NT;
   const int64_t i0 = (int64_t)threadIdx.x * per;
   const int64_t i1 = i0 + per < n ? i0 + per : n;
+  constexpr int COLS = NT / 16;   // columns of one digit that a thread scans
   K *src = keys, *dst = tmp;
   for (int shift = 0; shift < key_bits; shift += 4) {
-    for (int d = 0; d < 16; ++d) cnt[d][threadIdx.x] = 0;
-    for (int64_t i = i0; i < i1; ++i) cnt[(src[i] >> shift) & 15][threadIdx.x] += 1;
+    for (int d = 0; d < 16; ++d) cnt[d * NT + threadIdx.x] = 0;
+    for (int64_t i = i0; i < i1; ++i) cnt[((src[i] >> shift) & 15) * NT + threadIdx.x] += 1;
     __syncthreads();
-    // exclusive offsets in (digit, thread) order: thread t owns digit t / 16's
-    // columns 16 (t % 16) .. 16 (t % 16) + 15
-    const int dg = threadIdx.x / 16, c0 = (threadIdx.x % 16) * 16;
+    // exclusive offsets in (digit, thread) order: thread t owns the 16 counts
+    // from 16 t on, which lie in one digit's row
+    uint32_t *mine = cnt + (threadIdx.x / COLS) * NT + (threadIdx.x % COLS) * 16;
     uint32_t loc = 0;
-    for (int c = 0; c < 16; ++c) loc += cnt[dg][c0 + c];
+    for (int c = 0; c < 16; ++c) loc += mine[c];
     uint32_t tot;
-    uint32_t run = block_excl_scan<uint32_t>(loc, shs, &tot);
-    __syncthreads();
+    uint32_t run = block_excl_scan<uint32_t, NT>(loc, shs, &tot);
     for (int c = 0; c < 16; ++c) {
-      const uint32_t x = cnt[dg][c0 + c];
-      cnt[dg][c0 + c] = run;
+      const uint32_t x = mine[c];
+      mine[c] = run;
       run += x;
     }
     __syncthreads();
     for (int64_t i = i0; i < i1; ++i) {
       const K k = src[i];
       const int d = (int)((k >> shift) & 15);
-      dst[cnt[d][threadIdx.x]++] = k;
+      dst[cnt[d * NT + threadIdx.x]++] = k;
     }
     __syncthreads();
     K *t = src;
@@ -297,16 +352,68 @@ __device__ void block_sort(K *keys, int64_t n, K *tmp, int key_bits) {
     dst = t;
   }
   if (src != keys)
-    for (int64_t i = threadIdx.x; i < n; i += BT) keys[i] = src[i];
+    for (int64_t i = threadIdx.x; i < n; i += NT) keys[i] = src[i];
   __syncthreads();
 }
 
-// one block per bucket: its ids ascending
-__global__ void __launch_bounds__(BT) k_build_sort_ids(uint32_t *ids, const uint64_t *boff,
-                                                        uint32_t *tmp) {
-  const int64_t c = blockIdx.x;
-  const uint64_t s0 = boff[c], s1 = boff[c + 1];
-  block_sort<uint32_t>(ids + s0, (int64_t)(s1 - s0), tmp + s0, 32);
+// Buckets (or multi-cluster buckets) that one wave does not take go to two
+// lists, appended in any order (each is independent work): mid, for blocks of
+// BT threads, and big, for blocks of BIG threads.  Most buckets hold a few
+// rows, so one wave per bucket and four buckets per block keep the chip full
+// where one block per bucket left most lanes idle; the few large buckets,
+// whose chains end the kernel, get 1024 threads each.
+constexpr int WAVE_ROWS = WAVE;   // rows of a bucket sorted and seeded by one wave
+constexpr int MID_ROWS = BT;      // and by a block of BT threads
+constexpr int BIG = 1024;
+constexpr int LIST_GRID = 2048;   // blocks that walk a list
+
+struct SizeLists {
+  uint32_t *mid, *big;
+  uint32_t *count;  // [2], zero before the wave kernel
+};
+
+__device__ __forceinline__ void list_bucket(const SizeLists &l, int64_t m, uint32_t c) {
+  if (m <= MID_ROWS) l.mid[atomicAdd(&l.count[0], 1u)] = c;
+  else l.big[atomicAdd(&l.count[1], 1u)] = c;
+}
+
+// the ids of every bucket ascending: one wave per bucket of at most 64 rows
+__global__ void __launch_bounds__(BT) k_build_sort_wave(uint32_t *ids, const uint64_t *boff,
+                                                        int64_t nb, SizeLists l) {
+  const int lane = lane_id();
+  const int64_t c = (int64_t)blockIdx.x * (BT / WAVE) + threadIdx.x / WAVE;
+  if (c >= nb) return;
+  const uint64_t s0 = boff[c];
+  const int64_t m = (int64_t)(boff[c + 1] - s0);
+  if (m <= 1) return;
+  if (m > WAVE_ROWS) {
+    if (lane == 0) list_bucket(l, m, (uint32_t)c);
+    return;
+  }
+  uint32_t key = lane < m ? ids[s0 + lane] : 0xffffffffu;
+  int top = 2;
+  while (top < m) top <<= 1;
+  for (int k = 2; k <= top; k <<= 1)
+    for (int j = k >> 1; j > 0; j >>= 1) {
+      const uint32_t o = (uint32_t)__shfl_xor((int)key, j);
+      const bool up = (lane & k) == 0, lower = (lane & j) == 0;
+      key = (lower == up) == (key < o) ? key : o;
+    }
+  if (lane < m) ids[s0 + lane] = key;
+}
+
+template <int NT>
+__global__ void __launch_bounds__(NT) k_build_sort_list(uint32_t *ids, const uint64_t *boff,
+                                                        uint32_t *tmp, const uint32_t *list,
+                                                        const uint32_t *count) {
+  __shared__ uint32_t lds[SORT_LDS];
+  __shared__ uint32_t cnt[16 * NT];
+  __shared__ uint32_t shs[NT / WAVE];
+  const uint32_t total = *count;
+  for (uint32_t i = blockIdx.x; i < total; i += gridDim.x) {
+    const uint64_t s0 = boff[list[i]], s1 = boff[list[i] + 1];
+    block_sort<NT, uint32_t>(ids + s0, (int64_t)(s1 - s0), tmp + s0, 32, lds, cnt, shs);
+  }
 }
 
 // ------------------------------------------------------------------ k-means
@@ -318,131 +425,429 @@ struct KmArgs {
   const uint32_t *kb;       // [nb]
   const uint64_t *kbpre;    // [nb + 1] exclusive scan of kb: cluster slots of a bucket
   const uint32_t *mlist;    // [n_multi] buckets with kb >= 2, ascending
+  int64_t n_multi;
   const double *U;          // [n_multi x kmax]
   int kmax;
   uint32_t seed;
-  int lloyd, spc;
-  uint64_t *skey;           // [n] scratch: sample keys, in bucket order
+  int spc;
+  uint64_t *skey;           // [n] scratch: sample keys, in bucket order (big buckets)
   uint64_t *skey_tmp;       // [n] sort scratch
   double *d2;               // [n] scratch
-  uint32_t *label;          // [n] label of each member (bucket order), renumbered at the end
-  double *cent;             // [max_clusters x b] centres, by slot
-  uint32_t *ccnt;           // [max_clusters] members per slot
-  uint32_t *nkept;          // [nb] clusters kept per bucket (written for multi buckets)
+  uint32_t *label;          // [n] slot within its bucket of each member (bucket order)
+  double *cent;             // [slots x bp] centres, by slot
+  int bp;                   // b rounded up to a multiple of 4; zeros from b on
+  uint32_t *ccnt;           // [slots] members per slot
+  const uint4 *slot;        // [slots] see k_build_slots
+  int64_t slots;
+  uint32_t *changed;        // [nb] last Lloyd pass (from 1) that changed a label of the bucket
+  uint2 *tile;              // [n / 64 + n_multi] (bucket, first member) of 64 members each
+  uint32_t *ntile;          // zero before the tiles are listed
+  uint32_t *nkept;          // [nb] clusters kept per bucket (multi buckets; zero before)
 };
 
-__global__ void __launch_bounds__(BT) k_build_kmeans(KmArgs a) {
-  __shared__ int64_t sh64[BT / WAVE];
-  __shared__ uint32_t shu[BT / WAVE];
-  __shared__ int64_t s_pick;
-  const int mi = blockIdx.x;
+__device__ __forceinline__ uint64_t sample_key(uint32_t id, uint32_t seed) {
+  return ((uint64_t)mix32_dev(id, seed) << 32) | id;
+}
+
+// members of a bucket's sample
+__device__ __forceinline__ int64_t sample_size(int64_t m, int K, int spc) {
+  int64_t S = m;
+  if ((int64_t)spc * K < S) S = (int64_t)spc * K;
+  if (S > (int64_t)(1 << 21)) S = (int64_t)1 << 21;
+  return S;
+}
+
+// Rows and centres of b dimensions are handled as BP of them, zeros from b on
+// (BP >= b a template argument): a zero dimension adds +0 to a squared
+// distance, which leaves its bits, and the loads of a row have no branch
+// between them.
+template <int BP>
+__device__ __forceinline__ void load_row(float (&x)[BP], const float *r, int b) {
+#pragma unroll
+  for (int j = 0; j < BP; ++j) x[j] = r[j < b ? j : 0];
+#pragma unroll
+  for (int j = 0; j < BP; ++j) x[j] = j < b ? x[j] : 0.0f;
+}
+
+// fp64 squared distance, dimensions in order
+template <int BP>
+__device__ __forceinline__ double sqd(const float (&x)[BP], const float (&c)[BP]) {
+  double acc = 0.0;
+#pragma unroll
+  for (int j = 0; j < BP; ++j) {
+    const double t = (double)x[j] - (double)c[j];
+    acc = acc + t * t;
+  }
+  return acc;
+}
+
+// inclusive scan over the wave of values below 2^26, by DPP moves (rows of 16
+// lanes, then row totals onto the rows after them)
+__device__ __forceinline__ uint32_t dpp_incl_scan(uint32_t v) {
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, false);  // row_shr:1
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, false);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, false);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, false);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false);  // row_bcast:15
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false);  // row_bcast:31
+  return v;
+}
+
+// inclusive scan of weights of at most 2^30 each, as two halves of 15 bits
+// (the shuffles of a 64-bit scan take ten times as long, and every draw of the
+// k-means++ waits for one)
+__device__ __forceinline__ int64_t weight_incl_scan(int64_t w) {
+  const uint32_t lo = dpp_incl_scan((uint32_t)w & 0x7FFFu);
+  const uint32_t hi = dpp_incl_scan((uint32_t)w >> 15);
+  return ((int64_t)hi << 15) + (int64_t)lo;
+}
+
+// k-means++ of a bucket of at most 64 rows by one wave, a sample member per
+// lane: its row and D^2 stay in registers, the running weights are a wave scan
+template <int BP>
+__global__ void __launch_bounds__(BT) k_build_seed_wave(KmArgs a, SizeLists l) {
+  const int lane = lane_id();
+  const int64_t mi = (int64_t)blockIdx.x * (BT / WAVE) + threadIdx.x / WAVE;
+  if (mi >= a.n_multi) return;
   const uint32_t code = a.mlist[mi];
   const uint64_t s0 = a.boff[code];
   const int64_t m = (int64_t)(a.boff[code + 1] - s0);
-  const int K = (int)a.kb[code];
-  const int b = a.b;
-  const uint32_t *mid = a.ids + s0;
-  double *C = a.cent + a.kbpre[code] * b;
-  uint32_t *cnt = a.ccnt + a.kbpre[code];
-  uint32_t *lab = a.label + s0;
-  double *D2 = a.d2 + s0;
-  // the sample: members by (mix32(id), id), the first S of them
-  uint64_t *sk = a.skey + s0;
-  for (int64_t i = threadIdx.x; i < m; i += BT)
-    sk[i] = ((uint64_t)mix32_dev(mid[i], a.seed) << 32) | mid[i];
-  __syncthreads();
-  block_sort<uint64_t>(sk, m, a.skey_tmp + s0, 64);
-  int64_t S = m;
-  if ((int64_t)a.spc * K < S) S = (int64_t)a.spc * K;
-  if (S > (int64_t)(1 << 21)) S = (int64_t)1 << 21;
-  // k-means++: the first centre is the first sampled member
-  {
-    const float *x0 = a.lg + (uint64_t)(uint32_t)sk[0] * b;
-    for (int j = threadIdx.x; j < b; j += BT) C[j] = (double)x0[j];
+  if (m > WAVE_ROWS) {
+    if (lane == 0) list_bucket(l, m, (uint32_t)mi);
+    return;
   }
-  __syncthreads();
-  for (int64_t s = threadIdx.x; s < S; s += BT)
-    D2[s] = sqd_row(a.lg + (uint64_t)(uint32_t)sk[s] * b, C, b);
-  __syncthreads();
-  const int64_t per = (S + BT - 1) / BT;
-  const int64_t c0 = (int64_t)threadIdx.x * per;
-  const int64_t c1 = c0 + per < S ? c0 + per : S;
-  for (int r = 1; r < K; ++r) {
+  const int K = (int)a.kb[code], b = a.b;
+  double *C = a.cent + a.kbpre[code] * a.bp;
+  const int S = (int)sample_size(m, K, a.spc);
+  uint64_t key = lane < m ? sample_key(a.ids[s0 + lane], a.seed) : ~0ull;
+  key = wave_sort_u64(key, (int)m);
+  const uint32_t id = lane < S ? (uint32_t)key : (uint32_t)bcast_u64(key, 0);
+  float x[BP], c[BP];
+  load_row<BP>(x, a.lg + (uint64_t)id * b, b);
+  uint32_t pid = bcast_u32(id, 0);
+  double d2 = 0.0;
+  const double us = lane < K ? a.U[mi * a.kmax + lane] : 0.0;   // K <= 64: a uniform per lane
+  uint32_t drawn = 0;   // lane r: the id of draw r
+  for (int r = 0; r < K; ++r) {
+    if (r > 0) {
+      const int64_t w = lane < S ? d2_weight(d2) : 0;
+      const int64_t incl = weight_incl_scan(w);
+      const int64_t tot = (int64_t)bcast_u64((uint64_t)incl, WAVE - 1);
+      int pick = 0;
+      if (tot > 0) {
+        const double u = __longlong_as_double(
+            (long long)bcast_u64((uint64_t)__double_as_longlong(us), r));
+        const int64_t target = (int64_t)floor(u * (double)tot);
+        const uint64_t over = ballot(incl > target);
+        pick = over ? __ffsll((unsigned long long)over) - 1 : S - 1;
+      }
+      pid = bcast_u32(id, pick);
+    }
+    if (lane == r) drawn = pid;
+    load_row<BP>(c, a.lg + (uint64_t)pid * b, b);
+    const double d = sqd<BP>(x, c);
+    if (r == 0 || d < d2) d2 = d;
+  }
+  for (int e = lane; e < (K * a.bp + WAVE - 1) / WAVE * WAVE; e += WAVE) {
+    const int r = e / a.bp, j = e - r * a.bp;
+    const uint32_t rid = (uint32_t)__shfl((int)drawn, r < K ? r : 0);
+    if (r < K) C[e] = j < b ? (double)a.lg[(uint64_t)rid * b + j] : 0.0;
+  }
+}
+
+// k-means++ of a listed bucket by a block of NT threads.  Thread t owns the
+// sample members [t per, (t + 1) per); up to PT of them stay in registers with
+// their D^2.  The update of D^2 by a new centre also sums the thread's weights
+// for the next draw, so a draw costs one block scan, two barriers and the load
+// of one row; the draws are kept in LDS and the centres written at the end,
+// and the uniforms read 64 at a time, because a barrier waits for every load
+// and store before it (376 draws among 1128 rows of 16: 3.7 ms with them and
+// with the members past the first in memory).
+template <int NT, int BP>
+__global__ void __launch_bounds__(NT) k_build_seed_list(KmArgs a, const uint32_t *list,
+                                                        const uint32_t *count) {
+  constexpr int NW = NT / WAVE;
+  constexpr int PT = BP <= 16 ? 2 : 1;
+  __shared__ uint64_t keys[SORT_LDS];
+  __shared__ uint32_t cnt[16 * NT];   // counts of the sort, then the draws
+  __shared__ uint32_t shs[NW];
+  __shared__ int64_t s_tot[2][NW];
+  __shared__ int64_t s_pick[2];
+  const int lane = lane_id(), wv = threadIdx.x / WAVE;
+  const uint32_t total = *count;
+  for (uint32_t li = blockIdx.x; li < total; li += gridDim.x) {
+    const int64_t mi = list[li];
+    const uint32_t code = a.mlist[mi];
+    const uint64_t s0 = a.boff[code];
+    const int64_t m = (int64_t)(a.boff[code + 1] - s0);
+    const int K = (int)a.kb[code], b = a.b;
+    const uint32_t *mid = a.ids + s0;
+    double *C = a.cent + a.kbpre[code] * a.bp;
+    double *D2 = a.d2 + s0;
+    uint64_t *sk = a.skey + s0;
+    const double *U = a.U + mi * a.kmax;
+    for (int64_t i = threadIdx.x; i < m; i += NT) sk[i] = sample_key(mid[i], a.seed);
+    __syncthreads();
+    block_sort<NT, uint64_t>(sk, m, a.skey_tmp + s0, 64, keys, cnt, shs);
+    const int64_t S = sample_size(m, K, a.spc);
+    const int64_t per = (S + NT - 1) / NT;
+    const int64_t c0 = (int64_t)threadIdx.x * per < S ? (int64_t)threadIdx.x * per : S;
+    const int64_t c1 = c0 + per < S ? c0 + per : S;
+    const bool regs = per <= PT;
+    const bool in_lds = m <= SORT_LDS;  // the sort leaves its keys there too
+    auto sample_id = [&](int64_t i) -> uint32_t {
+      if (in_lds) return reinterpret_cast<const uint32_t *>(keys)[2 * (int)i];  // the low word
+      return (uint32_t)sk[i];
+    };
+    float x[PT][BP], c[BP];
+    double d2[PT];
+#pragma unroll
+    for (int t = 0; t < PT; ++t) {
+      d2[t] = 0.0;
+      if (regs) load_row<BP>(x[t], a.lg + (uint64_t)sample_id(c0 + t < c1 ? c0 + t : 0) * b, b);
+    }
+    if (threadIdx.x == 0) s_pick[0] = s_pick[1] = S;
+    uint32_t pid = sample_id(0);
     int64_t wsum = 0;
-    for (int64_t s = c0; s < c1; ++s) wsum += d2_weight(D2[s]);
-    int64_t tot;
-    int64_t run = block_excl_scan<int64_t>(wsum, sh64, &tot);
-    if (threadIdx.x == 0) s_pick = S;
-    __syncthreads();
-    int64_t pick = 0;
-    if (tot > 0) {
-      const int64_t target = (int64_t)floor(a.U[(int64_t)mi * a.kmax + r] * (double)tot);
-      int64_t mine = S;
-      for (int64_t s = c0; s < c1; ++s) {
-        run += d2_weight(D2[s]);
-        if (run > target) {
-          mine = s;
-          break;
+    double us = 0.0;   // lane l: the uniform of draw r with r % 64 = l
+    for (int r = 0; r < K; ++r) {
+      if ((r & (WAVE - 1)) == 0) us = r + lane < K ? U[r + lane] : 0.0;
+      if (r > 0) {
+        const int p = r & 1;
+        const int64_t incl = per == 1 ? weight_incl_scan(wsum)
+                                      : (int64_t)wave_incl_scan_u64((uint64_t)wsum);
+        if (lane == WAVE - 1) s_tot[p][wv] = incl;
+        __syncthreads();
+        if (threadIdx.x == 0) s_pick[p ^ 1] = S;   // read by all before this barrier
+        int64_t before = incl - wsum, tot = 0;
+#pragma unroll
+        for (int i = 0; i < NW; ++i) {
+          const int64_t v = s_tot[p][i];
+          before += i < wv ? v : 0;
+          tot += v;
+        }
+        if (tot > 0) {   // the same in every thread
+          const double u = __longlong_as_double(
+              (long long)bcast_u64((uint64_t)__double_as_longlong(us), r & (WAVE - 1)));
+          const int64_t target = (int64_t)floor(u * (double)tot);
+          if (before <= target && target < before + wsum) {
+            int64_t at = c0;
+            int64_t run = before;
+            if (regs) {
+#pragma unroll
+              for (int t = 0; t < PT; ++t) {
+                const bool more = at == c0 + t && at + 1 < c1;
+                if (more) run += d2_weight(d2[t]);
+                if (more && run <= target) ++at;
+              }
+            } else {
+              for (; at + 1 < c1; ++at) {
+                run += d2_weight(D2[at]);
+                if (run > target) break;
+              }
+            }
+            s_pick[p] = at;
+          }
+        }
+        __syncthreads();
+        int64_t pick = 0;
+        if (tot > 0) pick = s_pick[p] < S ? s_pick[p] : S - 1;
+        pid = (uint32_t)__builtin_amdgcn_readfirstlane((int)sample_id(pick));
+      }
+      const float *xp = a.lg + (uint64_t)pid * b;
+      load_row<BP>(c, xp, b);
+      if (r < 16 * NT) {
+        if (threadIdx.x == 0) cnt[r] = pid;
+      } else if ((int)threadIdx.x < a.bp) {
+        C[(int64_t)r * a.bp + threadIdx.x] = (int)threadIdx.x < b ? (double)xp[threadIdx.x] : 0.0;
+      }
+      wsum = 0;
+      if (regs) {
+#pragma unroll
+        for (int t = 0; t < PT; ++t) {
+          const double d = sqd<BP>(x[t], c);
+          if (r == 0 || d < d2[t]) d2[t] = d;
+          if (c0 + t < c1) wsum += d2_weight(d2[t]);
+        }
+      } else {
+        for (int64_t s = c0; s < c1; ++s) {
+          load_row<BP>(x[0], a.lg + (uint64_t)sample_id(s) * b, b);
+          const double d = sqd<BP>(x[0], c);
+          const double o = r == 0 ? d : D2[s];
+          const double v = d < o ? d : o;
+          D2[s] = v;
+          wsum += d2_weight(v);
         }
       }
-      if (mine < S) atomicMin((unsigned long long *)&s_pick, (unsigned long long)mine);
-      __syncthreads();
-      pick = s_pick < S ? s_pick : S - 1;
-    }
-    const float *xp = a.lg + (uint64_t)(uint32_t)sk[pick] * b;
-    for (int j = threadIdx.x; j < b; j += BT) C[(int64_t)r * b + j] = (double)xp[j];
-    __syncthreads();
-    for (int64_t s = threadIdx.x; s < S; s += BT) {
-      const double d = sqd_row(a.lg + (uint64_t)(uint32_t)sk[s] * b, C + (int64_t)r * b, b);
-      if (d < D2[s]) D2[s] = d;
     }
     __syncthreads();
+    const int64_t kept = (int64_t)(K < 16 * NT ? K : 16 * NT) * a.bp;
+    for (int64_t e = threadIdx.x; e < kept; e += NT) {
+      const int r = (int)(e / a.bp), j = (int)(e - (int64_t)r * a.bp);
+      C[e] = j < b ? (double)a.lg[(uint64_t)cnt[r] * b + j] : 0.0;
+    }
+    __syncthreads();   // the next bucket's sort reuses the block's LDS
   }
-  // Lloyd passes over every member (in id order)
-  for (int it = 0; it < a.lloyd; ++it) {
-    for (int64_t i = threadIdx.x; i < m; i += BT) {
-      const float *x = a.lg + (uint64_t)mid[i] * b;
-      double best = sqd_row(x, C, b);
-      int bk = 0;
-      for (int k = 1; k < K; ++k) {
-        const double d = sqd_row(x, C + (int64_t)k * b, b);
-        if (d < best) {
-          best = d;
-          bk = k;
-        }
+}
+
+// The slots of every bucket, 64 buckets per wave (those of one slot each by
+// their own lane): (first row, rows, slot within the bucket, bucket), so that
+// the waves that take a slot each start from one load
+__global__ void __launch_bounds__(BT) k_build_slots(const uint32_t *kb, const uint64_t *kbpre,
+                                                    const uint64_t *boff, int64_t nb,
+                                                    int64_t slots, uint4 *slot) {
+  const int lane = lane_id();
+  const int64_t w0 = (int64_t)blockIdx.x * (BT / WAVE) + threadIdx.x / WAVE;
+  const int64_t c = w0 * WAVE + lane;
+  const uint32_t k = c < nb ? kb[c] : 0u;
+  const uint64_t p = c < nb ? kbpre[c] : 0ull;
+  const uint32_t s0 = c < nb ? (uint32_t)boff[c] : 0u;
+  const uint32_t m = c < nb ? (uint32_t)boff[c + 1] - s0 : 0u;
+  if (k == 1 && (int64_t)p < slots) slot[p] = make_uint4(s0, m, 0u, (uint32_t)c);
+  uint64_t many = ballot(k > 1);
+  while (many) {
+    const int src = __ffsll((unsigned long long)many) - 1;
+    many &= many - 1;
+    const uint64_t ps = bcast_u64(p, src);
+    const uint32_t ks = bcast_u32(k, src), ss = bcast_u32(s0, src), ms = bcast_u32(m, src);
+    for (uint32_t i = lane; i < ks; i += WAVE)
+      if ((int64_t)(ps + i) < slots)
+        slot[ps + i] = make_uint4(ss, ms, i, (uint32_t)(w0 * WAVE + src));
+  }
+}
+
+// the multi-cluster buckets' members, 64 to a tile; 64 buckets per wave, one
+// atomic each
+__global__ void __launch_bounds__(BT) k_build_tiles(KmArgs a) {
+  const int lane = lane_id();
+  const int64_t mi = ((int64_t)blockIdx.x * (BT / WAVE) + threadIdx.x / WAVE) * WAVE + lane;
+  uint32_t code = 0, nt = 0;
+  if (mi < a.n_multi) {
+    code = a.mlist[mi];
+    nt = ((uint32_t)(a.boff[code + 1] - a.boff[code]) + WAVE - 1) / WAVE;
+  }
+  const uint32_t incl = wave_incl_scan_u32(nt);
+  uint32_t base = 0;
+  if (lane == WAVE - 1) base = atomicAdd(a.ntile, incl);
+  base = bcast_u32(base, WAVE - 1) + incl - nt;
+  if (nt == 1) a.tile[base] = make_uint2(code, 0u);
+  uint64_t many = ballot(nt > 1);
+  while (many) {
+    const int src = __ffsll((unsigned long long)many) - 1;
+    many &= many - 1;
+    const uint32_t n = bcast_u32(nt, src), at = bcast_u32(base, src), cd = bcast_u32(code, src);
+    for (uint32_t t = lane; t < n; t += WAVE) a.tile[at + t] = make_uint2(cd, t * WAVE);
+  }
+}
+
+// Lloyd, first half: the nearest centre of each member, one wave per tile.
+// Every member of a tile has the same centres, so they are read once per wave
+// (scalar loads, two centres in flight) and the fp64 arithmetic bounds the
+// pass.  A bucket in which the last pass changed no label is at rest: its
+// centres and labels stay as they are.
+template <int BP>
+__global__ void __launch_bounds__(BT) k_build_assign(KmArgs a, uint32_t pass) {
+  const int lane = lane_id();
+  const uint32_t t = (uint32_t)__builtin_amdgcn_readfirstlane(
+      (int)(blockIdx.x * (BT / WAVE) + threadIdx.x / WAVE));
+  if (t >= *a.ntile) return;
+  const uint2 tl = a.tile[t];
+  const uint32_t code = (uint32_t)__builtin_amdgcn_readfirstlane((int)tl.x);
+  const uint32_t i0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)tl.y);
+  // passes count from 1; another tile of the bucket may store this pass's number
+  if (pass > 1 && a.changed[code] + 1 < pass) return;
+  const uint64_t s0 = a.boff[code];
+  const uint32_t m = (uint32_t)(a.boff[code + 1] - s0);
+  const int K = (int)a.kb[code], b = a.b;
+  const double *__restrict__ C = a.cent + a.kbpre[code] * BP;
+  const uint32_t i = i0 + lane;
+  const bool in = i < m;
+  float xf[BP];
+  load_row<BP>(xf, a.lg + (uint64_t)a.ids[s0 + (in ? i : i0)] * b, b);
+  double x[BP];
+#pragma unroll
+  for (int j = 0; j < BP; ++j) x[j] = (double)xf[j];
+  double best = INFINITY;
+  uint32_t bk = 0;
+#pragma unroll 2
+  for (int k = 0; k < K; ++k) {
+    const double *c = C + (int64_t)k * BP;
+    double acc = 0.0;
+#pragma unroll
+    for (int j = 0; j < BP; ++j) {
+      const double d = x[j] - c[j];
+      acc = acc + d * d;
+    }
+    if (k == 0 || acc < best) {
+      best = acc;
+      bk = (uint32_t)k;
+    }
+  }
+  const bool moved = in && (pass == 1 || a.label[s0 + i] != bk);
+  if (moved) a.label[s0 + i] = bk;
+  if (ballot(moved) && lane == 0) a.changed[code] = pass;
+}
+
+// the wave's lanes j < b add row[id][j] of the members whose lanes are set in
+// `mask`, in lane order, eight rows in flight (the order of the additions is
+// the result's; only their loads run ahead)
+__device__ __forceinline__ void ordered_add(double &sum, const float *lg, int b, uint32_t id,
+                                            uint64_t mask) {
+  const int j = lane_id() < b ? lane_id() : 0;
+  while (mask) {
+    float v[8];
+    int n = 0;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      v[u] = 0.0f;
+      if (mask) {
+        const int src = __ffsll((unsigned long long)mask) - 1;
+        mask &= mask - 1;
+        v[u] = lg[(uint64_t)bcast_u32(id, src) * b + j];
+        ++n;
       }
-      lab[i] = (uint32_t)bk;
     }
-    __syncthreads();
-    // each (k, j) sums its members in id order
-    for (int kj = threadIdx.x; kj < K * b; kj += BT) {
-      const int k = kj / b, j = kj % b;
-      double sum = 0.0;
-      uint32_t n_k = 0;
-      for (int64_t i = 0; i < m; ++i)
-        if (lab[i] == (uint32_t)k) {
-          sum = sum + (double)a.lg[(uint64_t)mid[i] * b + j];
-          ++n_k;
-        }
-      if (n_k > 0) C[(int64_t)k * b + j] = sum / (double)n_k;
-      if (j == 0) cnt[k] = n_k;
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      if (u < n) sum = sum + (double)v[u];
+  }
+}
+
+// Lloyd, second half: one wave per slot finds its members 64 labels at a time
+// and adds them in id order
+__global__ void __launch_bounds__(BT) k_build_update(KmArgs a, uint32_t pass, int last) {
+  const int lane = lane_id();
+  const int64_t sl = (int64_t)blockIdx.x * (BT / WAVE) + threadIdx.x / WAVE;
+  if (sl >= a.slots) return;
+  const uint4 rec = a.slot[sl];
+  const uint32_t code = rec.w, m = rec.y, k = rec.z;
+  if (m == 0 || a.kb[code] < 2) return;
+  uint32_t n_k = 0;
+  if (a.changed[code] == pass) {
+    const uint32_t *label = a.label + rec.x, *ids = a.ids + rec.x;
+    double sum = 0.0;
+    for (uint32_t r0 = 0; r0 < m; r0 += 4 * WAVE) {
+      uint32_t lab[4], id[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const uint32_t i = r0 + u * WAVE + lane;
+        lab[u] = i < m ? label[i] : 0xffffffffu;
+        id[u] = i < m ? ids[i] : 0u;
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        const uint64_t mk = ballot(lab[u] == k);
+        if (!mk) continue;
+        n_k += (uint32_t)popc64(mk);
+        ordered_add(sum, a.lg, a.b, id[u], mk);
+      }
     }
-    __syncthreads();
+    if (n_k > 0 && lane < a.b) a.cent[sl * a.bp + lane] = sum / (double)n_k;
+    if (lane == 0) a.ccnt[sl] = n_k;
+  } else if (last) {
+    n_k = a.ccnt[sl];
   }
-  // kept clusters (non-empty), renumbered in order
-  if (threadIdx.x == 0) {
-    uint32_t nk = 0;
-    for (int k = 0; k < K; ++k) nk += cnt[k] > 0 ? 1u : 0u;
-    a.nkept[code] = nk;
-  }
-  __syncthreads();
-  for (int64_t i = threadIdx.x; i < m; i += BT) {
-    const uint32_t k = lab[i];
-    uint32_t nr = 0;
-    for (uint32_t k2 = 0; k2 < k; ++k2) nr += cnt[k2] > 0 ? 1u : 0u;
-    lab[i] = nr;
-  }
-  (void)shu;
+  if (last && lane == 0 && n_k > 0) atomicAdd(&a.nkept[code], 1u);
 }
 
 // clusters of each bucket: 0 (empty), 1 (K_B = 1) or the kept count
@@ -460,63 +865,87 @@ struct FinArgs {
   const uint32_t *ids, *kb, *label, *ccnt;
   const uint64_t *kbpre;
   const double *cent;
+  int bp;
+  const uint4 *slot;
+  int64_t slots;
   const uint32_t *bc_off;
   int64_t *row_ids;        // [n] out
   uint64_t *csize;         // [n_clusters] out: rows per cluster
   float *centroids;        // [n_clusters x b] out
 };
 
-// one block per bucket: rows in (cluster, id) order, cluster sizes, centroids
+// one wave per slot: its cluster's rows in (cluster, id) order, size and
+// centroid.  Empty slots are dropped, so a slot's cluster number and first row
+// come from the counts of its bucket's earlier slots
 __global__ void __launch_bounds__(BT) k_build_finish(FinArgs a) {
-  __shared__ uint32_t shu[BT / WAVE];
-  const int64_t c = blockIdx.x;
-  const uint64_t s0 = a.boff[c];
-  const int64_t m = (int64_t)(a.boff[c + 1] - s0);
+  const int lane = lane_id();
+  const int64_t sl = (int64_t)blockIdx.x * (BT / WAVE) + threadIdx.x / WAVE;
+  if (sl >= a.slots) return;
+  const uint4 rec = a.slot[sl];
+  const uint32_t c = rec.w, m = rec.y, k = rec.z;
   if (m == 0) return;
+  const uint64_t s0 = rec.x;
   const int b = a.b;
   const uint32_t *mid = a.ids + s0;
   const uint32_t g0 = a.bc_off[c];
   if (a.kb[c] < 2) {  // one cluster: rows in id order, fp64 mean in id order
-    for (int64_t i = threadIdx.x; i < m; i += BT) a.row_ids[s0 + i] = mid[i];
-    for (int j = threadIdx.x; j < b; j += BT) {
-      double sum = 0.0;
-      for (int64_t i = 0; i < m; ++i) sum = sum + (double)a.lg[(uint64_t)mid[i] * b + j];
-      a.centroids[(uint64_t)g0 * b + j] = (float)(sum / (double)m);
+    double sum = 0.0;
+    for (uint32_t r0 = 0; r0 < m; r0 += WAVE) {
+      const uint32_t i = r0 + lane;
+      const uint32_t id = i < m ? mid[i] : 0u;
+      if (i < m) a.row_ids[s0 + i] = id;
+      ordered_add(sum, a.lg, b, id, ballot(i < m));
     }
-    if (threadIdx.x == 0) a.csize[g0] = (uint64_t)m;
+    if (lane < b) a.centroids[(uint64_t)g0 * b + lane] = (float)(sum / (double)m);
+    if (lane == 0) a.csize[g0] = m;
     return;
   }
-  const uint32_t nk = a.bc_off[c + 1] - g0;
-  const uint32_t *lab = a.label + s0;
-  const uint32_t K = a.kb[c];
-  const uint64_t slot0 = a.kbpre[c];
-  // kept slots in order -> clusters g0 .. g0 + nk - 1
-  uint64_t pos = s0;
-  uint32_t kk = 0;
-  for (uint32_t k = 0; k < K; ++k) {
-    const uint32_t n_k = a.ccnt[slot0 + k];
-    if (n_k == 0) continue;
-    const uint32_t g = g0 + kk;
-    for (int j = threadIdx.x; j < b; j += BT)
-      a.centroids[(uint64_t)g * b + j] = (float)a.cent[(slot0 + k) * b + j];
-    if (threadIdx.x == 0) a.csize[g] = n_k;
-    // members with label kk, in id order: a block scan per round of BT members
-    for (int64_t r0 = 0; r0 < m; r0 += BT) {
-      const int64_t i = r0 + threadIdx.x;
-      const uint32_t f = (i < m && lab[i] == kk) ? 1u : 0u;
-      uint32_t tot;
-      const uint32_t ex = block_excl_scan<uint32_t>(f, shu, &tot);
-      if (f) a.row_ids[pos + ex] = mid[i];
-      pos += tot;
-      __syncthreads();
-    }
-    ++kk;
+  const uint32_t n_k = a.ccnt[sl];
+  if (n_k == 0) return;
+  const int64_t slot0 = sl - k;
+  uint32_t kept = 0, rows = 0;  // clusters and rows of the slots before
+  for (uint32_t k0 = 0; k0 < k; k0 += WAVE) {
+    const uint32_t v = k0 + lane < k ? a.ccnt[slot0 + k0 + lane] : 0u;
+    kept += (uint32_t)popc64(ballot(v > 0));
+    rows += wave_sum_u32(v);
   }
-  (void)nk;
+  const uint32_t g = g0 + kept;
+  if (lane < b) a.centroids[(uint64_t)g * b + lane] = (float)a.cent[sl * a.bp + lane];
+  if (lane == 0) a.csize[g] = n_k;
+  uint64_t pos = s0 + rows;
+  for (uint32_t r0 = 0; r0 < m; r0 += WAVE) {
+    const uint32_t i = r0 + lane;
+    const bool f = i < m && a.label[s0 + i] == k;
+    const uint64_t mk = ballot(f);
+    if (f) a.row_ids[pos + popc64(mk & lanemask_lt())] = mid[i];
+    pos += (uint64_t)popc64(mk);
+  }
 }
 
 // ------------------------------------------------------------------ launches
-hipError_t launch_build_tau(const float *lg, int64_t ns, int b, float *tau, hipStream_t s) {
+// work space of the whole-chip select, or 0 for samples that one block per
+// dimension selects in about the launches' time (eight of them)
+size_t build_tau_ws(int64_t ns, int b) {
+  if (ns < TAU_SMALL || ns > 0xffffffffll) return 0;
+  return (size_t)b * (256 * sizeof(uint32_t) + sizeof(TauState));
+}
+
+hipError_t launch_build_tau(const float *lg, int64_t ns, int b, float *tau, void *ws,
+                            hipStream_t s) {
+  if (ws) {
+    TauState *st = static_cast<TauState *>(ws);
+    uint32_t *hist = reinterpret_cast<uint32_t *>(st + b);
+    const int64_t per = 4 * (BT / b);   // rows per step of a block
+    const int64_t g = (ns + per - 1) / per;
+    hipLaunchKernelGGL(k_tau_init, dim3((unsigned)b), dim3(256), 0, s, st, hist, b,
+                       (uint32_t)((ns - 1) / 2));
+    for (int shift = 24; shift >= 0; shift -= 8) {
+      hipLaunchKernelGGL(k_tau_hist, dim3((unsigned)(g < 1024 ? g : 1024)), dim3(BT),
+                         (size_t)b * 1024, s, lg, ns, b, shift, st, hist);
+      hipLaunchKernelGGL(k_tau_pick, dim3((unsigned)b), dim3(256), 0, s, hist, st, shift, tau);
+    }
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(k_build_tau, dim3((unsigned)b), dim3(BT), 0, s, lg, ns, b, tau);
   return hipGetLastError();
 }
@@ -584,6 +1013,22 @@ hipError_t run_build_plan(const BuildArgs &A, hipStream_t s) {
   return hipGetLastError();
 }
 
+// blocks of the kernels that walk a list of at most `items` buckets
+static dim3 list_grid(int64_t items) {
+  return dim3((unsigned)(items < LIST_GRID ? (items > 0 ? items : 1) : LIST_GRID));
+}
+
+template <int BP>
+static void launch_seeds(const KmArgs &k, const SizeLists &l, int64_t n, hipStream_t s) {
+  const int64_t wpb = BT / WAVE;
+  hipLaunchKernelGGL(k_build_seed_wave<BP>, dim3((unsigned)((k.n_multi + wpb - 1) / wpb)),
+                     dim3(BT), 0, s, k, l);
+  hipLaunchKernelGGL((k_build_seed_list<BT, BP>), list_grid(k.n_multi), dim3(BT), 0, s, k, l.mid,
+                     l.count);
+  hipLaunchKernelGGL((k_build_seed_list<BIG, BP>), list_grid(n / MID_ROWS), dim3(BIG), 0, s, k,
+                     l.big, l.count + 1);
+}
+
 hipError_t run_build_index(const BuildArgs &A, hipStream_t s) {
   const int64_t nb = (int64_t)1 << A.b;
   const int64_t n = A.n;
@@ -594,9 +1039,19 @@ hipError_t run_build_index(const BuildArgs &A, hipStream_t s) {
   if ((e = launch_fill_i32((int32_t *)A.cursor, nb, 0, s)) != hipSuccess) return e;
   hipLaunchKernelGGL(k_build_scatter, grid_for(n), dim3(BT), 0, s, A.codes, n, A.boff, A.cursor,
                      A.ids);
-  hipLaunchKernelGGL(k_build_sort_ids, dim3((unsigned)nb), dim3(BT), 0, s, A.ids, A.boff,
-                     A.ids_tmp);
+  const int64_t wpb = BT / WAVE;  // buckets, slots or tiles per block, a wave each
+  auto waves = [&](int64_t items) { return dim3((unsigned)((items + wpb - 1) / wpb)); };
+  const SizeLists l{A.list_mid, A.list_big, A.counts};
+  if ((e = launch_fill_i32((int32_t *)A.counts, 5, 0, s)) != hipSuccess) return e;
+  hipLaunchKernelGGL(k_build_sort_wave, waves(nb), dim3(BT), 0, s, A.ids, A.boff, nb, l);
+  hipLaunchKernelGGL(k_build_sort_list<BT>, list_grid(nb), dim3(BT), 0, s, A.ids, A.boff,
+                     A.ids_tmp, l.mid, l.count);
+  hipLaunchKernelGGL(k_build_sort_list<BIG>, list_grid(n / MID_ROWS), dim3(BIG), 0, s, A.ids,
+                     A.boff, A.ids_tmp, l.big, l.count + 1);
   if ((e = hipGetLastError()) != hipSuccess) return e;
+  if ((e = launch_fill_i32((int32_t *)A.slot, 4 * A.slots, 0, s)) != hipSuccess) return e;
+  hipLaunchKernelGGL(k_build_slots, waves((nb + WAVE - 1) / WAVE), dim3(BT), 0, s, A.kb, A.kbpre,
+                     A.boff, nb, A.slots, A.slot);
   // k-means of the multi-cluster buckets
   if ((e = launch_fill_i32((int32_t *)A.nkept, nb, 0, s)) != hipSuccess) return e;
   if (A.n_multi > 0) {
@@ -608,10 +1063,10 @@ hipError_t run_build_index(const BuildArgs &A, hipStream_t s) {
     k.kb = A.kb;
     k.kbpre = A.kbpre;
     k.mlist = A.mlist;
+    k.n_multi = A.n_multi;
     k.U = A.U;
     k.kmax = A.kmax;
     k.seed = A.seed;
-    k.lloyd = A.lloyd;
     k.spc = A.spc;
     k.skey = A.skey;
     k.skey_tmp = A.skey_tmp;
@@ -619,8 +1074,37 @@ hipError_t run_build_index(const BuildArgs &A, hipStream_t s) {
     k.label = A.label;
     k.cent = A.cent;
     k.ccnt = A.ccnt;
+    k.bp = build_pad(A.b);
+    k.slot = A.slot;
+    k.slots = A.slots;
+    k.changed = A.changed;
+    k.tile = A.tile;
+    k.ntile = A.counts + 4;
     k.nkept = A.nkept;
-    hipLaunchKernelGGL(k_build_kmeans, dim3((unsigned)A.n_multi), dim3(BT), 0, s, k);
+    const SizeLists lm{A.list_mid, A.list_big, A.counts + 2};
+    hipLaunchKernelGGL(k_build_tiles, waves((A.n_multi + WAVE - 1) / WAVE), dim3(BT), 0, s, k);
+    switch ((A.b + 7) / 8) {
+      case 1: launch_seeds<8>(k, lm, n, s); break;
+      case 2: launch_seeds<16>(k, lm, n, s); break;
+      case 3: launch_seeds<24>(k, lm, n, s); break;
+      default: launch_seeds<32>(k, lm, n, s); break;
+    }
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    const dim3 ga = waves(n / WAVE + A.n_multi);
+    for (int it = 1; it <= A.lloyd; ++it) {
+      switch (k.bp / 4) {
+        case 1: hipLaunchKernelGGL(k_build_assign<4>, ga, dim3(BT), 0, s, k, (uint32_t)it); break;
+        case 2: hipLaunchKernelGGL(k_build_assign<8>, ga, dim3(BT), 0, s, k, (uint32_t)it); break;
+        case 3: hipLaunchKernelGGL(k_build_assign<12>, ga, dim3(BT), 0, s, k, (uint32_t)it); break;
+        case 4: hipLaunchKernelGGL(k_build_assign<16>, ga, dim3(BT), 0, s, k, (uint32_t)it); break;
+        case 5: hipLaunchKernelGGL(k_build_assign<20>, ga, dim3(BT), 0, s, k, (uint32_t)it); break;
+        case 6: hipLaunchKernelGGL(k_build_assign<24>, ga, dim3(BT), 0, s, k, (uint32_t)it); break;
+        case 7: hipLaunchKernelGGL(k_build_assign<28>, ga, dim3(BT), 0, s, k, (uint32_t)it); break;
+        default: hipLaunchKernelGGL(k_build_assign<32>, ga, dim3(BT), 0, s, k, (uint32_t)it); break;
+      }
+      hipLaunchKernelGGL(k_build_update, waves(A.slots), dim3(BT), 0, s, k, (uint32_t)it,
+                         it == A.lloyd ? 1 : 0);
+    }
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   // directory, rows, cluster sizes, centroids
@@ -636,11 +1120,14 @@ hipError_t run_build_index(const BuildArgs &A, hipStream_t s) {
   f.ccnt = A.ccnt;
   f.kbpre = A.kbpre;
   f.cent = A.cent;
+  f.bp = build_pad(A.b);
+  f.slot = A.slot;
+  f.slots = A.slots;
   f.bc_off = A.bc_off;
   f.row_ids = A.row_ids;
   f.csize = A.csize;
   f.centroids = A.centroids;
-  hipLaunchKernelGGL(k_build_finish, dim3((unsigned)nb), dim3(BT), 0, s, f);
+  hipLaunchKernelGGL(k_build_finish, waves(A.slots), dim3(BT), 0, s, f);
   return hipGetLastError();
 }
 

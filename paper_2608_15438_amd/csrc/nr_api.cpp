@@ -1220,7 +1220,18 @@ nr_status nr_lsim_grad(const float *d2_emb, const float *lat, int64_t B, int32_t
 nr_status nr_build_tau(const float *logits, int64_t ns, int32_t b, float *tau, hipStream_t stream) {
   if (ns < 1 || b < 1 || b > 30) return fail(NR_EINVAL, "ns must be >= 1 and b in [1, 30]");
   if (!logits || !tau) return fail(NR_EINVAL, "NULL buffer");
-  HIP_OK(nr::launch_build_tau(logits, ns, b, tau, stream));
+  // stream-ordered work space; without it (a stream being captured keeps its
+  // one kernel, and so does a device out of memory) one block per dimension
+  void *ws = nullptr;
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  const size_t bytes = nr::build_tau_ws(ns, b);
+  if (bytes > 0 && hipStreamIsCapturing(stream, &cap) == hipSuccess &&
+      cap == hipStreamCaptureStatusNone && hipMallocAsync(&ws, bytes, stream) != hipSuccess)
+    ws = nullptr;
+  (void)hipGetLastError();
+  const hipError_t e = nr::launch_build_tau(logits, ns, b, tau, ws, stream);
+  if (ws) HIP_OK(hipFreeAsync(ws, stream));
+  HIP_OK(e);
   return NR_OK;
 }
 
@@ -1314,25 +1325,37 @@ nr_status nr_build_index(const nr_build_desc *d, int64_t *row_ids, uint32_t *bc_
   a.seed = d->seed;
   a.lloyd = d->lloyd;
   a.spc = d->sample_per_cluster;
+  a.slots = mc;
   const int64_t most = std::max(std::max(nb, n), mc) + 1;
-  a.blk = ds.get<uint64_t>(nr::build_scan_blocks(most));
-  a.kbpre = ds.get<uint64_t>(nb + 1);
-  a.boff = ds.get<uint64_t>(nb + 1);
-  a.cursor = ds.get<uint32_t>(nb);
-  a.nkept = ds.get<uint32_t>(nb);
-  a.ncl = ds.get<uint32_t>(nb);
-  a.ids = ds.get<uint32_t>(n);
-  a.ids_tmp = ds.get<uint32_t>(n);
-  a.label = ds.get<uint32_t>(n);
-  a.skey = ds.get<uint64_t>(n);
-  a.skey_tmp = ds.get<uint64_t>(n);
-  a.d2 = ds.get<double>(n);
-  a.cent = ds.get<double>((size_t)mc * d->b);
-  a.ccnt = ds.get<uint32_t>(mc);
-  a.csize = ds.get<uint64_t>(mc);
-  if (!a.blk || !a.kbpre || !a.boff || !a.cursor || !a.nkept || !a.ncl || !a.ids || !a.ids_tmp ||
-      !a.label || !a.skey || !a.skey_tmp || !a.d2 || !a.cent || !a.ccnt || !a.csize)
-    return fail(NR_ENOMEM, "build scratch allocation failed");
+  // one allocation for all scratch arrays
+  auto take_all = [&](char *base) {
+    Carver c{base};
+    a.blk = c.take<uint64_t>(nr::build_scan_blocks(most));
+    a.kbpre = c.take<uint64_t>(nb + 1);
+    a.boff = c.take<uint64_t>(nb + 1);
+    a.cursor = c.take<uint32_t>(nb);
+    a.nkept = c.take<uint32_t>(nb);
+    a.ncl = c.take<uint32_t>(nb);
+    a.ids = c.take<uint32_t>(n);
+    a.ids_tmp = c.take<uint32_t>(n);
+    a.label = c.take<uint32_t>(n);
+    a.skey = c.take<uint64_t>(n);
+    a.skey_tmp = c.take<uint64_t>(n);
+    a.d2 = c.take<double>(n);
+    a.cent = c.take<double>((size_t)mc * nr::build_pad(d->b));
+    a.ccnt = c.take<uint32_t>(mc);
+    a.slot = c.take<uint4>(mc);
+    a.changed = c.take<uint32_t>(nb);
+    a.list_mid = c.take<uint32_t>(n / 64 + 1);
+    a.list_big = c.take<uint32_t>(n / 256 + 1);
+    a.counts = c.take<uint32_t>(5);
+    a.tile = c.take<uint2>(n / 64 + (d->n_multi > 0 ? d->n_multi : 0) + 1);
+    a.csize = c.take<uint64_t>(mc);
+    return c.off;
+  };
+  char *base = ds.get<char>(take_all(nullptr));
+  if (!base) return fail(NR_ENOMEM, "build scratch allocation failed");
+  take_all(base);
   a.bc_off = bc_off;
   a.row_ids = row_ids;
   a.centroids = centroids;

@@ -388,15 +388,24 @@ struct BuildArgs {
   int kmax;
   uint32_t seed;
   int lloyd, spc;
-  double *cent;               // [max_clusters x b]
-  uint32_t *ccnt;             // [max_clusters]
+  int64_t slots;              // max_clusters: cluster slots of all buckets
+  double *cent;               // [slots x build_pad(b)]
+  uint32_t *ccnt;             // [slots]
+  uint4 *slot;                // [slots]
+  uint32_t *changed;          // [2^b]
+  uint32_t *list_mid, *list_big;  // [n / 64 + 1], [n / 256 + 1] buckets by size
+  uint32_t *counts;           // [5] the lists' lengths and the number of tiles
+  uint2 *tile;                // [n / 64 + n_multi + 1]
   uint32_t *bc_off;           // [2^b + 1] out
   int64_t *row_ids;           // [n] out
   uint64_t *csize;            // [max_clusters]
   float *centroids;           // [max_clusters x b] out
 };
 size_t build_scan_blocks(int64_t n);
-hipError_t launch_build_tau(const float *lg, int64_t ns, int b, float *tau, hipStream_t s);
+int build_pad(int b);  // doubles per centre: b rounded up to a multiple of 4
+size_t build_tau_ws(int64_t ns, int b);
+hipError_t launch_build_tau(const float *lg, int64_t ns, int b, float *tau, void *ws,
+                            hipStream_t s);
 hipError_t launch_build_codes(const float *lg, int64_t m, int b, const float *tau, uint32_t *codes,
                               uint32_t *sizes, hipStream_t s);
 hipError_t launch_build_nonempty(const uint32_t *sizes, int64_t nb, unsigned long long *out,
