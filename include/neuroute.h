@@ -294,6 +294,17 @@ nr_status nr_pair_sqdist(const float *x, int64_t B, int32_t D, float *ws, float 
 nr_status nr_lsim_grad(const float *d2_emb, const float *lat, int64_t B, int32_t L,
                        float gamma_rho, float tau_emb, double *num_cnt, float *grad_lat,
                        hipStream_t stream);
+/* tau_emb of a batch without a copy to the host: nr_pair_quantile writes to
+ * out (DEVICE fp64 [1]) the q-quantile (linear interpolation, the rank in
+ * fp32) of the first `limit` (at most 2^24) off-diagonal elements of d2_emb
+ * in row order; ws: DEVICE scratch of nr_pair_quantile_ws() bytes.
+ * nr_lsim_grad_at is nr_lsim_grad with tau_emb = sqrt(*tau_sq). */
+size_t nr_pair_quantile_ws(void);
+nr_status nr_pair_quantile(const float *d2_emb, int64_t B, int64_t limit, float q, void *ws,
+                           double *out, hipStream_t stream);
+nr_status nr_lsim_grad_at(const float *d2_emb, const float *lat, int64_t B, int32_t L,
+                          float gamma_rho, const double *tau_sq, double *num_cnt,
+                          float *grad_lat, hipStream_t stream);
 
 /* ---- Index construction on the GPU (Sec. 3.3 "Bucket allocation" and
  * "In-bucket clustering"; thresholds, Sec. 3.2.3).  Untimed, run once.

@@ -1213,7 +1213,36 @@ nr_status nr_lsim_grad(const float *d2_emb, const float *lat, int64_t B, int32_t
   if (!std::isfinite(gamma_rho) || !std::isfinite(tau_emb))
     return fail(NR_EINVAL, "gamma_rho and tau_emb must be finite");
   if (!d2_emb || !lat || !num_cnt || !grad_lat) return fail(NR_EINVAL, "NULL buffer");
-  HIP_OK(nr::launch_lsim_grad(d2_emb, lat, B, L, gamma_rho, tau_emb, num_cnt, grad_lat, stream));
+  HIP_OK(nr::launch_lsim_grad(d2_emb, lat, B, L, gamma_rho, tau_emb, nullptr, num_cnt, grad_lat,
+                              stream));
+  return NR_OK;
+}
+
+size_t nr_pair_quantile_ws(void) { return nr::pair_quantile_ws_bytes(); }
+
+nr_status nr_pair_quantile(const float *d2_emb, int64_t B, int64_t limit, float q, void *ws,
+                           double *out, hipStream_t stream) {
+  if (B < 2 || limit < 1) return fail(NR_EINVAL, "B must be >= 2 and limit >= 1");
+  if (B > 65536) return fail(NR_EUNSUPPORTED, "B %lld > 65536", (long long)B);
+  if (!(q >= 0.0f && q <= 1.0f)) return fail(NR_EINVAL, "q must be in [0, 1]");
+  if (!d2_emb || !ws || !out) return fail(NR_EINVAL, "NULL buffer");
+  const int64_t all = B * (B - 1);
+  const int64_t n = limit < all ? limit : all;
+  if (n > (int64_t)1 << 24) return fail(NR_EUNSUPPORTED, "limit must be at most 2^24");
+  HIP_OK(nr::launch_pair_quantile(d2_emb, B, n, q, ws, out, stream));
+  return NR_OK;
+}
+
+nr_status nr_lsim_grad_at(const float *d2_emb, const float *lat, int64_t B, int32_t L,
+                          float gamma_rho, const double *tau_sq, double *num_cnt,
+                          float *grad_lat, hipStream_t stream) {
+  if (B < 0 || L < 1) return fail(NR_EINVAL, "B must be >= 0 and L >= 1");
+  if (L > 32) return fail(NR_EUNSUPPORTED, "L %d > 32", L);
+  if (B > 65536) return fail(NR_EUNSUPPORTED, "B %lld > 65536", (long long)B);
+  if (!std::isfinite(gamma_rho)) return fail(NR_EINVAL, "gamma_rho must be finite");
+  if (!d2_emb || !lat || !tau_sq || !num_cnt || !grad_lat) return fail(NR_EINVAL, "NULL buffer");
+  HIP_OK(nr::launch_lsim_grad(d2_emb, lat, B, L, gamma_rho, 0.0f, tau_sq, num_cnt, grad_lat,
+                              stream));
   return NR_OK;
 }
 

@@ -420,7 +420,11 @@ size_t pair_sqdist_ws_floats(int64_t B, int D);
 hipError_t launch_pair_sqdist(const float *x, int64_t B, int D, float *ws, float *out,
                               hipStream_t s);
 hipError_t launch_lsim_grad(const float *d2, const float *lat, int64_t B, int L, float gr,
-                            float tau, double *num_cnt, float *grad, hipStream_t s);
+                            float tau, const double *tau2, double *num_cnt, float *grad,
+                            hipStream_t s);
+size_t pair_quantile_ws_bytes();
+hipError_t launch_pair_quantile(const float *d2, int64_t B, int64_t n, float q, void *ws,
+                                double *out, hipStream_t s);
 
 hipError_t launch_stream_read(const void *buf, int64_t bytes, uint32_t *sink, int n_cu,
                               hipStream_t s);

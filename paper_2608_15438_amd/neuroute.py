@@ -39,6 +39,7 @@ WORK = ("tiles", "rows", "rows_read", "own_rows", "shared_rows", "shared_pairs",
 # every symbol include/neuroute.h declares
 EXPORTS = ("nr_index_upload", "nr_index_free", "nr_search", "nr_search_ex", "nr_search_noalloc",
            "nr_encode", "nr_calibrate", "nr_pair_sqdist_ws", "nr_pair_sqdist", "nr_lsim_grad",
+           "nr_pair_quantile_ws", "nr_pair_quantile", "nr_lsim_grad_at",
            "nr_build_tau", "nr_build_codes", "nr_build_plan", "nr_build_index",
            "nr_probe", "nr_route", "nr_route_capacity", "nr_refine", "nr_profile_enable",
            "nr_profile_read", "nr_last_work", "nr_stream_read", "nr_status_string",
@@ -119,6 +120,10 @@ def lib():
         L.nr_pair_sqdist_ws.restype = C.c_size_t
         L.nr_pair_sqdist.argtypes = [P, C.c_int64, C.c_int32, P, P, P]
         L.nr_lsim_grad.argtypes = [P, P, C.c_int64, C.c_int32, C.c_float, C.c_float, P, P, P]
+        L.nr_pair_quantile_ws.argtypes = []
+        L.nr_pair_quantile_ws.restype = C.c_size_t
+        L.nr_pair_quantile.argtypes = [P, C.c_int64, C.c_int64, C.c_float, P, P, P]
+        L.nr_lsim_grad_at.argtypes = [P, P, C.c_int64, C.c_int32, C.c_float, P, P, P, P]
         L.nr_build_tau.argtypes = [P, C.c_int64, C.c_int32, P, P]
         L.nr_build_codes.argtypes = [P, C.c_int64, C.c_int32, P, P, P, P]
         L.nr_build_plan.argtypes = [P, C.c_int64, C.c_int32, C.c_int32, C.c_uint32, P, P,
@@ -211,6 +216,32 @@ def nr_lsim_grad(d2_emb: torch.Tensor, lat: torch.Tensor, gamma_rho: float, tau_
     _check(lib().nr_lsim_grad(_ptr(d2_emb), _ptr(lat), B, L, float(gamma_rho), float(tau_emb),
                               _ptr(num_cnt), _ptr(grad), _stream(stream)), "nr_lsim_grad")
     return num_cnt, grad
+
+
+def nr_pair_quantile(d2_emb: torch.Tensor, q: float, limit: int = 1 << 24, out=None, stream=None):
+    """fp64 [1] (device): the q-quantile of the first `limit` off-diagonal
+    elements of the distances d2_emb [B, B]."""
+    _dev(d2_emb, "d2_emb")
+    ws = torch.empty(int(lib().nr_pair_quantile_ws()), dtype=torch.uint8, device=d2_emb.device)
+    if out is None:
+        out = torch.empty(1, dtype=torch.float64, device=d2_emb.device)
+    _check(lib().nr_pair_quantile(_ptr(d2_emb), d2_emb.shape[0], limit, float(q), _ptr(ws),
+                                  _ptr(out), _stream(stream)), "nr_pair_quantile")
+    return out
+
+
+def nr_lsim_grad_at(d2_emb: torch.Tensor, lat: torch.Tensor, gamma_rho: float,
+                    stats: torch.Tensor, stream=None):
+    """nr_lsim_grad with tau_emb = sqrt(stats[2]) read on the device; (sum, count)
+    go to stats[:2] (fp64 [3]).  Returns grad_lat fp32 [B, L]."""
+    _dev(d2_emb, "d2_emb")
+    _dev(lat, "lat")
+    B, L = lat.shape
+    grad = torch.empty((B, L), dtype=torch.float32, device=lat.device)
+    _check(lib().nr_lsim_grad_at(_ptr(d2_emb), _ptr(lat), B, L, float(gamma_rho),
+                                 C.c_void_p(stats.data_ptr() + 16), _ptr(stats), _ptr(grad),
+                                 _stream(stream)), "nr_lsim_grad_at")
+    return grad
 
 
 def nr_build_tau(logits: torch.Tensor, stream=None):

@@ -82,12 +82,22 @@ def lsim_loss_gpu(x: torch.Tensor, lat: torch.Tensor, gamma: float,
     L = lat.shape[1]
     gr = gamma * math.sqrt(L / E)
     d2 = NR.nr_pair_sqdist(x.float().contiguous())
-    if tau_emb is None:
-        off = ~torch.eye(B, dtype=torch.bool, device=x.device)
-        tau_emb = math.sqrt(float(torch.quantile(d2[off][: 1 << 24], quantile)))
-    num_cnt, grad = NR.nr_lsim_grad(d2, lat.detach().float().contiguous(), gr, tau_emb)
-    loss = _LsimGpu.apply(lat, num_cnt, grad)
-    return loss, tau_emb, float(num_cnt[1]) / (B * (B - 1))
+    l32 = lat.detach().float().contiguous()
+    if tau_emb is not None:
+        num_cnt, grad = NR.nr_lsim_grad(d2, l32, gr, tau_emb)
+        loss = _LsimGpu.apply(lat, num_cnt, grad)
+        return loss, tau_emb, float(num_cnt[1]) / (B * (B - 1))
+    if B < 2:
+        raise RuntimeError("quantile() input tensor must be non-empty")
+    if not 0 <= quantile <= 1:
+        raise RuntimeError("quantile() q must be in the range [0, 1]")
+    # (sum, count, tau_emb^2) stay on the device until the gradient is under way
+    stats = torch.empty(3, dtype=torch.float64, device=lat.device)
+    NR.nr_pair_quantile(d2, quantile, out=stats[2:])
+    grad = NR.nr_lsim_grad_at(d2, l32, gr, stats)
+    loss = _LsimGpu.apply(lat, stats[:2], grad)
+    _, cnt, tau_sq = stats.tolist()
+    return loss, math.sqrt(tau_sq), cnt / (B * (B - 1))
 
 
 class _Mlp(torch.nn.Module):
