@@ -136,8 +136,8 @@ __global__ void __launch_bounds__(1024) k_plan_scan(PlanArgs a) {
   }
   if (tid == 1023) {
     a.tile_off[a.nq] = part[1023];
-    *a.counter = 0;
   }
+  if (tid < TILE_COUNTERS) a.counter[tid * TILE_COUNTER_STRIDE] = 0;
 }
 
 // one thread per (query, tile slot): tile -> query and first cluster
@@ -169,104 +169,113 @@ hipError_t launch_plan(const PlanArgs &a, hipStream_t s) {
 }
 
 // ------------------------------------------------------------------ top-k in lanes
-// Lanes 0..k-1 hold a list sorted by (key, id); `kth` is the last entry when full.
-struct TopK {
-  uint32_t key;
-  int64_t id;
-  int cnt;
-  uint32_t kth_key;
-  int64_t kth_id;
-};
-
-__device__ __forceinline__ void topk_init(TopK &t) {
-  t.key = 0xffffffffu;
-  t.id = -1;
-  t.cnt = 0;
-  t.kth_key = 0xffffffffu;
-  t.kth_id = INT64_MAX;
-}
-
-// insert (ck, cid) if it ranks among the k best (wave-uniform arguments)
-__device__ __forceinline__ void topk_insert(TopK &t, int k, uint32_t ck, int64_t cid) {
-  const int lane = lane_id();
-  if (t.cnt == k && (ck > t.kth_key || (ck == t.kth_key && cid >= t.kth_id))) return;
-  const bool less = lane < t.cnt && (t.key < ck || (t.key == ck && t.id < cid));
-  const int pos = popc64(ballot(less));
-  const uint32_t up_key = (uint32_t)__shfl_up((int)t.key, 1);
-  const int64_t up_id = (int64_t)shfl_up_u64((uint64_t)t.id, 1);
-  if (lane == pos) { t.key = ck; t.id = cid; }
-  else if (lane > pos && lane < k) { t.key = up_key; t.id = up_id; }
-  t.cnt = t.cnt + 1 < k ? t.cnt + 1 : k;
-  if (t.cnt == k) {
-    t.kth_key = bcast_u32(t.key, k - 1);
-    t.kth_id = (int64_t)bcast_u64((uint64_t)t.id, k - 1);
-  }
-}
-
-// The refinement's running top-k: like TopK, but an entry's original id is
+// The refinement's running top-k: lanes 0..k-1 hold a list sorted by (key,
+// id), kth_key is the last entry's key when full.  An entry's original id is
 // read only when it decides something -- a candidate whose key equals a key in
 // the list (ids order equal keys) -- or when the tile's list is written out,
 // so the row loop does not wait for id loads.  Entries keep their payload row
-// (phys) until then; `known` marks the lanes whose id has been read.
+// (phys) until then; id is UNREAD.  Rows and ids are below 2^32 - 1.
+constexpr uint32_t UNREAD = 0xffffffffu;
 struct LazyTopK {
-  uint32_t key;
-  int64_t id;
-  uint64_t phys;
-  bool known;
+  uint32_t key, id, phys;
   int cnt;
   uint32_t kth_key;
 };
 
 __device__ __forceinline__ void ltopk_init(LazyTopK &t) {
   t.key = 0xffffffffu;
-  t.id = -1;
+  t.id = UNREAD;
   t.phys = 0;
-  t.known = true;
   t.cnt = 0;
   t.kth_key = 0xffffffffu;
 }
 
+// the value of the lane below (lane 0 keeps its own)
+__device__ __forceinline__ uint32_t lane_up1(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x138, 0xF, 0xF, false);
+}
+
 // insert the payload row cp with key ck if (ck, its id) ranks among the k best
-// (wave-uniform arguments); ids are ordered as in TopK
-__device__ __forceinline__ void ltopk_insert(LazyTopK &t, int k, uint32_t ck, uint64_t cp,
+// (wave-uniform arguments)
+__device__ __forceinline__ void ltopk_insert(LazyTopK &t, int k, uint32_t ck, uint32_t cp,
                                              const int64_t *row_ids) {
   const int lane = lane_id();
   if (t.cnt == k && ck > t.kth_key) return;
   // ids matter only among equal keys: read the candidate's and those of the
   // listed entries with its key (one round of loads, rare)
   const bool eq = lane < t.cnt && t.key == ck;
-  int64_t cid = -1;
-  bool cknown = false;
+  uint32_t cid = UNREAD;
   if (ballot(eq)) {
-    cid = row_ids[cp];
-    cknown = true;
-    if (eq && !t.known) {
-      t.id = row_ids[t.phys];
-      t.known = true;
-    }
+    cid = (uint32_t)row_ids[cp];
+    if (eq && t.id == UNREAD) t.id = (uint32_t)row_ids[t.phys];
     // a tie with the k-th entry: the candidate enters only below its id
-    if (t.cnt == k && ck == t.kth_key &&
-        cid >= (int64_t)bcast_u64((uint64_t)t.id, k - 1)) return;
+    if (t.cnt == k && ck == t.kth_key && cid >= bcast_u32(t.id, k - 1)) return;
   }
   const bool less = lane < t.cnt && (t.key < ck || (t.key == ck && t.id < cid));
   const int pos = popc64(ballot(less));
-  const uint32_t up_key = (uint32_t)__shfl_up((int)t.key, 1);
-  const int64_t up_id = (int64_t)shfl_up_u64((uint64_t)t.id, 1);
-  const uint64_t up_phys = shfl_up_u64(t.phys, 1);
-  const bool up_known = __shfl_up((int)t.known, 1) != 0;
+  const uint32_t up_key = lane_up1(t.key), up_id = lane_up1(t.id), up_phys = lane_up1(t.phys);
   if (lane == pos) {
     t.key = ck;
     t.id = cid;
     t.phys = cp;
-    t.known = cknown;
   } else if (lane > pos && lane < k) {
     t.key = up_key;
     t.id = up_id;
     t.phys = up_phys;
-    t.known = up_known;
   }
   t.cnt = t.cnt + 1 < k ? t.cnt + 1 : k;
   if (t.cnt == k) t.kth_key = bcast_u32(t.key, k - 1);
+}
+
+// Candidates of one step (one per lane of `m`, payload row cp), all at once:
+// their ids and the list's unread ones are loaded, the candidates sorted by
+// (key, id) -- ids are below 2^32 -- and merged with the list.  While a list
+// fills, a step of 64 rows holds tens of entrants: one such merge takes about
+// as long as three insertions.
+constexpr int BATCH_MIN = 5;   // entrants of a step from which they go together
+__device__ __forceinline__ void ltopk_batch(LazyTopK &t, int k, uint64_t m, uint32_t ck,
+                                            uint32_t cp, const int64_t *row_ids) {
+  const int lane = lane_id();
+  const bool in = (m >> lane) & 1ull;
+  uint32_t cid = 0;
+  if (in) cid = (uint32_t)row_ids[cp];
+  if (lane < t.cnt && t.id == UNREAD) t.id = (uint32_t)row_ids[t.phys];
+  const uint64_t cand = wave_sort_u64(in ? ((uint64_t)ck << 32) | cid : ~0ull);
+  const uint64_t list = lane < t.cnt ? ((uint64_t)t.key << 32) | t.id : ~0ull;
+  const uint64_t v = wave_merge_least_u64(list, cand);
+  const int n = t.cnt + popc64(m);
+  t.cnt = n < k ? n : k;
+  t.key = lane < t.cnt ? (uint32_t)(v >> 32) : 0xffffffffu;
+  t.id = (uint32_t)v;
+  if (t.cnt == k) t.kth_key = bcast_u32(t.key, k - 1);
+}
+
+// The rows of one step into the list.  Row 8 u + g of the step has its key in
+// every lane of group g; lane (g, gl) takes that of u = gl.  phys_of() gives
+// the payload row of the lane's own row (called only when a row may enter).
+template <int U, class Phys>
+__device__ __forceinline__ void ltopk_step(LazyTopK &t, int k, const uint32_t (&key)[U],
+                                           uint32_t rows_left, const int64_t *row_ids,
+                                           Phys phys_of) {
+  const int lane = lane_id(), g = lane >> 3, gl = lane & 7;
+  uint32_t kk = key[0];
+#pragma unroll
+  for (int u = 1; u < U; ++u) kk = gl == u ? key[u] : kk;
+  const bool in = gl < U && (uint32_t)(8 * gl + g) < rows_left;
+  uint64_t m = ballot(in && kk <= t.kth_key);
+  if (!m) return;
+  const uint32_t phys = phys_of();
+  if (popc64(m) >= BATCH_MIN) {
+    ltopk_batch(t, k, m, kk, phys, row_ids);
+    return;
+  }
+  while (m) {
+    const int src = __ffsll((unsigned long long)m) - 1;
+    m &= m - 1;
+    const uint32_t ck = bcast_u32(kk, src);
+    if (t.cnt == k && ck > t.kth_key) continue;
+    ltopk_insert(t, k, ck, bcast_u32(phys, src), row_ids);
+  }
 }
 
 // ------------------------------------------------------------------ refine
@@ -291,14 +300,20 @@ __global__ void __launch_bounds__(256, NSEG <= 1 ? NR_REFINE_WAVES1 : 1) k_refin
   const int total = a.tile_off[a.nq];
   const int rb = a.row_bytes;
   const int k = a.k;
-  if (total == 0) return;  // nothing to do: skip the counter (an empty redo launch)
-  unsigned long long nbytes = 0;  // row bytes this lane group read (its lane 0)
+  unsigned long long nbytes = 0;  // row bytes this lane (group) read
 
-  for (;;) {
-    int t = 0;
-    if (lane == 0) t = atomicAdd(a.counter, 1);
-    t = __builtin_amdgcn_readfirstlane(t);
-    if (t >= total) break;
+  // the wave's tiles: its own number where there are no more tiles than waves
+  // (a wave that has none then ends without an atomic), else those congruent
+  // to it modulo TILE_COUNTERS, in turn
+  const int nwaves = (int)gridDim.x * 4;
+  const int wid = __builtin_amdgcn_readfirstlane((int)blockIdx.x * 4 + w);
+  const int cg = wid % TILE_COUNTERS;
+  auto next_tile = [&]() __attribute__((always_inline)) {
+    int x = 0;
+    if (lane == 0) x = atomicAdd(&a.counter[cg * TILE_COUNTER_STRIDE], 1);
+    return __builtin_amdgcn_readfirstlane(x) * TILE_COUNTERS + cg;
+  };
+  for (int t = total <= nwaves ? wid : next_tile(); t < total;) {
     const int64_t q = a.tile_q[t];
     const uint32_t T = a.tsize[q];
     const uint32_t R = a.rtot[q];
@@ -427,27 +442,19 @@ __global__ void __launch_bounds__(256, NSEG <= 1 ? NR_REFINE_WAVES1 : 1) k_refin
               key[u] = __float_as_uint(acc);
             }
           }
-#pragma unroll
-          for (int u = 0; u < U; ++u) {
-            const bool ok = vb + 8 * u + g < vend;
-            if (ok && gl == 0) nbytes += (uint32_t)rb;
-            uint64_t m = ballot(ok && gl == 0 && key[u] <= tk.kth_key);
-            while (m) {
-              const int src = __ffsll((unsigned long long)m) - 1;
-              m &= m - 1;
-              const uint32_t ck = bcast_u32(key[u], src);
-              if (tk.cnt == k && ck > tk.kth_key) continue;
-              // the entrant's payload row: the last staged cluster starting
-              // at or before its virtual row
-              const uint32_t rv = vb + 8 * u + (uint32_t)(src >> 3);
-              int lo = 0, hi = ns - 1;
-              while (lo < hi) {
-                const int mid = (lo + hi + 1) >> 1;
-                if (vs[mid] <= rv) lo = mid; else hi = mid - 1;
-              }
-              ltopk_insert(tk, k, ck, ps[lo] + (rv - vs[lo]), a.row_ids);
+          // a row's payload index: the last staged cluster starting at or
+          // before its virtual row
+          const uint32_t left = vend - vb;
+          if (lane == 0) nbytes += (unsigned long long)(left < 8 * U ? left : 8 * U) * (uint32_t)rb;
+          ltopk_step<U>(tk, k, key, left, a.row_ids, [&]() -> uint32_t {
+            const uint32_t rv = vb + 8 * gl + g;
+            int lo = 0, hi = ns - 1;
+            while (lo < hi) {
+              const int mid = (lo + hi + 1) >> 1;
+              if (vs[mid] <= rv) lo = mid; else hi = mid - 1;
             }
-          }
+            return (uint32_t)ps[lo] + (rv - vs[lo]);
+          });
         };
         uint32_t vb = v;
         issue(vb, xa);
@@ -630,31 +637,32 @@ __global__ void __launch_bounds__(256, NSEG <= 1 ? NR_REFINE_WAVES1 : 1) k_refin
           }
         }
         }
-        // rows that may enter the top-k, in row order
+        // rows that may enter the top-k
+        const uint32_t left = vend - vb;
+        ltopk_step<U>(tk, k, key, left, a.row_ids, [&]() -> uint32_t {
+          uint32_t p = (uint32_t)phys[0];
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-          uint64_t m = ballot(ok[u] && gl == 0 && key[u] <= tk.kth_key);
-          while (m) {
-            const int src = __ffsll((unsigned long long)m) - 1;
-            m &= m - 1;
-            const uint32_t ck = bcast_u32(key[u], src);
-            if (tk.cnt == k && ck > tk.kth_key) continue;
-            ltopk_insert(tk, k, ck, bcast_u64(phys[u], src), a.row_ids);
-          }
-        }
+          for (int u = 1; u < U; ++u) p = gl == u ? (uint32_t)phys[u] : p;
+          return p;
+        });
       }
       v = vend;
       c += ns;
       __builtin_amdgcn_wave_barrier();
     }
     // partial result of this tile: the ids not read yet, all at once
-    if (lane < tk.cnt && !tk.known) tk.id = a.row_ids[tk.phys];
+    if (lane < tk.cnt && tk.id == UNREAD) tk.id = (uint32_t)a.row_ids[tk.phys];
     if (lane < k) {
       a.pkey[(int64_t)t * k + lane] = lane < tk.cnt ? tk.key : 0xffffffffu;
-      a.pid[(int64_t)t * k + lane] = lane < tk.cnt ? tk.id : -1;
+      a.pid[(int64_t)t * k + lane] = lane < tk.cnt ? (int64_t)tk.id : -1;
     }
+    if (total <= nwaves) break;
+    t = next_tile();
   }
-  if (a.rbytes && gl == 0 && nbytes) atomicAdd(a.rbytes, nbytes);
+  if (a.rbytes) {
+    for (int m = 1; m < WAVE; m <<= 1) nbytes += shfl_xor_u64(nbytes, m);
+    if (lane == 0 && nbytes) atomicAdd(a.rbytes, nbytes);
+  }
 }
 
 template <int IS_U8>
@@ -691,28 +699,27 @@ __global__ void __launch_bounds__(256) k_merge(MergeArgs a) {
   if (a.qmask && !a.qmask[q]) return;
   const int k = a.k;
   const int64_t e0 = (int64_t)a.tile_off[q] * k, e1 = (int64_t)a.tile_off[q + 1] * k;
-  TopK tk;
-  topk_init(tk);
-  for (int64_t i0 = e0; i0 < e1; i0 += WAVE) {
+  // (key, id) in one word (ids are below 2^32, -1 is an empty entry).  The
+  // tiles' lists are sorted; those of as many tiles as fit 64 lanes are sorted
+  // together, then merged with the best so far
+  uint64_t best = ~0ull;
+  const int64_t step = (int64_t)(WAVE / k) * k;
+  for (int64_t i0 = e0; i0 < e1; i0 += step) {
     const int64_t i = i0 + lane;
-    uint32_t key = 0xffffffffu;
-    int64_t id = -1;
-    if (i < e1) {
-      key = a.pkey[i];
-      id = a.pid[i];
+    uint64_t v = ~0ull;
+    if (lane < step && i < e1) {
+      const int64_t id = a.pid[i];
+      if (id >= 0) v = ((uint64_t)a.pkey[i] << 32) | (uint32_t)id;
     }
-    uint64_t m = ballot(id >= 0 && key <= tk.kth_key);
-    while (m) {
-      const int src = __ffsll((unsigned long long)m) - 1;
-      m &= m - 1;
-      topk_insert(tk, k, bcast_u32(key, src), (int64_t)bcast_u64((uint64_t)id, src));
-    }
+    if (step > k) v = wave_sort_u64(v);
+    best = i0 == e0 ? v : wave_merge_least_u64(best, v);
   }
   if (lane < k) {
-    const bool have = lane < tk.cnt;
-    a.out_ids[q * k + lane] = have ? tk.id : -1;
+    const bool have = best != ~0ull;
+    const uint32_t key = (uint32_t)(best >> 32);
+    a.out_ids[q * k + lane] = have ? (int64_t)(uint32_t)best : -1;
     a.out_dists[q * k + lane] =
-        have ? (a.is_u8 ? (float)tk.key : __uint_as_float(tk.key)) : INFINITY;
+        have ? (a.is_u8 ? (float)key : __uint_as_float(key)) : INFINITY;
   }
   if (lane == 0 && a.qstats) {
     a.qstats[q * NR_QSTATS + NR_QS_ROWS] = (int32_t)a.rtot[q];

@@ -370,7 +370,8 @@ hipError_t launch_shared_prep(const SharedArgs &a, hipStream_t s) {
   if (e == hipSuccess) e = launch_fill_i32((int32_t *)(a.wstats + 3), 6, 0, s);
   if (e == hipSuccess) e = launch_fill_i32((int32_t *)a.pool_cnt, 2, 0, s);
   if (e == hipSuccess) e = launch_fill_i32((int32_t *)a.open_cnt, 2, 0, s);
-  if (e == hipSuccess) e = launch_fill_i32((int32_t *)a.counter, 2, 0, s);
+  if (e == hipSuccess)
+    e = launch_fill_i32((int32_t *)a.counter, TILE_COUNTERS * TILE_COUNTER_STRIDE, 0, s);
   if (e != hipSuccess) return e;
   const int64_t nblk = list_blocks(a.n_clusters);
   hipLaunchKernelGGL(k_list_count, dim3((unsigned)nblk), dim3(LIST_THREADS), 0, s, a);
@@ -563,13 +564,20 @@ __global__ void __launch_bounds__(256, NSEG <= 1 ? NR_SCAN_WAVES1 : (NSEG > 8 ? 
   unsigned long long full_rows = 0, body_bytes = 0;
   uint32_t nbatch = 0, tested_batches = 0;  // direct batches: see below
   uint64_t tested_rows = 0, open_rows = 0;
-  if (ntiles == 0) return;
+  // wave w's tiles: its own number where there are no more tiles than waves
+  // (a wave that has none then ends without an atomic), else those congruent
+  // to w modulo TILE_COUNTERS, in turn
+  const uint32_t wid =
+      (uint32_t)__builtin_amdgcn_readfirstlane((int)(blockIdx.x * (256 / WAVE) + (uint32_t)w));
+  const uint32_t nwaves = gridDim.x * (256 / WAVE);
+  const uint32_t cg = wid % TILE_COUNTERS;
+  auto next_tile = [&]() __attribute__((always_inline)) -> uint64_t {
+    uint32_t x = 0;
+    if (lane == 0) x = atomicAdd(&a.counter[cg * TILE_COUNTER_STRIDE], 1u);
+    return (uint64_t)bcast_u32(x, 0) * TILE_COUNTERS + cg;
+  };
 
-  for (;;) {
-    unsigned long long t = 0;
-    if (lane == 0) t = atomicAdd(a.counter, 1ull);
-    t = bcast_u64(t, 0);
-    if (t >= ntiles) break;
+  for (uint64_t t = ntiles <= nwaves ? wid : next_tile(); t < ntiles;) {
     const uint64_t ws = (uint64_t)t * tile;
     const uint64_t we = ws + tile < W ? ws + tile : W;
     // the list entry holding ws: the last i with swork_off[i] <= ws (64-ary search)
@@ -1094,6 +1102,8 @@ __global__ void __launch_bounds__(256, NSEG <= 1 ? NR_SCAN_WAVES1 : (NSEG > 8 ? 
       open_rows += listed;
       __builtin_amdgcn_wave_barrier();
     }
+    if (ntiles <= nwaves) break;
+    t = next_tile();
   }
   if (lane == 0 && full_rows) atomicAdd((unsigned long long *)&a.wstats[3], full_rows);
   if (lane == 0 && body_bytes) atomicAdd((unsigned long long *)&a.wstats[4], body_bytes);
@@ -1228,36 +1238,6 @@ hipError_t launch_scan_open(const SharedArgs &a, int dtype, int n_cu, hipStream_
 }
 
 // ------------------------------------------------------------------ merge
-// (key, id) of a top-k list held in lanes 0..k-1
-struct SharedTopK {
-  uint32_t key;
-  int64_t id;
-  int cnt;
-  uint32_t kth_key;
-  int64_t kth_id;
-};
-
-__device__ __forceinline__ void stk_insert(SharedTopK &t, int k, uint32_t ck, int64_t cid) {
-  const int lane = lane_id();
-  if (t.cnt == k && (ck > t.kth_key || (ck == t.kth_key && cid >= t.kth_id))) return;
-  const bool less = lane < t.cnt && (t.key < ck || (t.key == ck && t.id < cid));
-  const int pos = popc64(ballot(less));
-  const uint32_t up_key = (uint32_t)__shfl_up((int)t.key, 1);
-  const int64_t up_id = (int64_t)shfl_up_u64((uint64_t)t.id, 1);
-  if (lane == pos) {
-    t.key = ck;
-    t.id = cid;
-  } else if (lane > pos && lane < k) {
-    t.key = up_key;
-    t.id = up_id;
-  }
-  t.cnt = t.cnt + 1 < k ? t.cnt + 1 : k;
-  if (t.cnt == k) {
-    t.kth_key = bcast_u32(t.key, k - 1);
-    t.kth_id = (int64_t)bcast_u64((uint64_t)t.id, k - 1);
-  }
-}
-
 // pooled survivors per query: offsets (one block scans the per-query counts)
 __global__ void __launch_bounds__(1024) k_pool_offsets(SharedArgs a) {
   __shared__ uint32_t part[1024];
@@ -1333,30 +1313,16 @@ __global__ void __launch_bounds__(256) k_shared_merge(SharedArgs a) {
   const int cnt = a.scnt[q];
   const int own = cnt < SURVIVOR_CAP ? cnt : SURVIVOR_CAP;
   const uint32_t p0 = a.poff[q];
-  SharedTopK tk;
-  tk.key = 0xffffffffu;
-  tk.id = -1;
-  tk.cnt = 0;
-  tk.kth_key = 0xffffffffu;
-  tk.kth_id = INT64_MAX;
-  // the seed top-k (sorted)
-  {
-    int64_t id = -1;
-    uint32_t key = 0xffffffffu;
-    if (lane < k) {
-      id = a.own_ids[q * k + lane];
-      const float d = a.own_dists[q * k + lane];
-      key = a.is_u8 ? (uint32_t)d : __float_as_uint(d);
-    }
-    uint64_t m = ballot(lane < k && id >= 0);
-    while (m) {
-      const int src = __ffsll((unsigned long long)m) - 1;
-      m &= m - 1;
-      stk_insert(tk, k, bcast_u32(key, src), (int64_t)bcast_u64((uint64_t)id, src));
-    }
+  // (key, id) in one word (ids are below 2^32); the seed top-k is sorted
+  uint64_t best = ~0ull;
+  if (lane < k) {
+    const int64_t id = a.own_ids[q * k + lane];
+    const float d = a.own_dists[q * k + lane];
+    if (id >= 0) best = ((uint64_t)(a.is_u8 ? (uint32_t)d : __float_as_uint(d)) << 32) | (uint32_t)id;
   }
   // survivors: the query's own slots, then its pooled ones; four chunks of
-  // 64 are loaded per round, ids only for keys that can still enter
+  // 64 are loaded per round, ids only for keys that can still enter; a chunk
+  // is sorted and merged at once
   constexpr int RC = 4;
   for (int r0 = 0; r0 < cnt; r0 += RC * WAVE) {
     uint32_t key[RC];
@@ -1370,23 +1336,25 @@ __global__ void __launch_bounds__(256) k_shared_merge(SharedArgs a) {
 #pragma unroll
     for (int u = 0; u < RC; ++u) {
       const int i = r0 + u * WAVE + lane;
-      uint64_t m = ballot(i < cnt && key[u] <= tk.kth_key);
-      if (!m) continue;
-      int64_t id = -1;
-      if ((m >> lane) & 1ull)
-        id = i < own ? a.sid[q * SURVIVOR_CAP + i] : a.pool2_id[p0 + (uint32_t)(i - SURVIVOR_CAP)];
-      while (m) {
-        const int src = __ffsll((unsigned long long)m) - 1;
-        m &= m - 1;
-        stk_insert(tk, k, bcast_u32(key[u], src), (int64_t)bcast_u64((uint64_t)id, src));
+      const uint32_t kth = bcast_u32((uint32_t)(best >> 32), k - 1);
+      const bool in = i < cnt && key[u] <= kth;
+      if (!ballot(in)) continue;
+      uint64_t v = ~0ull;
+      if (in) {
+        const int64_t id =
+            i < own ? a.sid[q * SURVIVOR_CAP + i] : a.pool2_id[p0 + (uint32_t)(i - SURVIVOR_CAP)];
+        v = ((uint64_t)key[u] << 32) | (uint32_t)id;
       }
+      best = wave_merge_least_u64(best, wave_sort_u64(v));
+      if (lane >= k) best = ~0ull;
     }
   }
   if (lane < k) {
-    const bool have = lane < tk.cnt;
-    a.out_ids[q * k + lane] = have ? tk.id : -1;
+    const bool have = best != ~0ull;
+    const uint32_t key = (uint32_t)(best >> 32);
+    a.out_ids[q * k + lane] = have ? (int64_t)(uint32_t)best : -1;
     a.out_dists[q * k + lane] =
-        have ? (a.is_u8 ? (float)tk.key : __uint_as_float(tk.key)) : INFINITY;
+        have ? (a.is_u8 ? (float)key : __uint_as_float(key)) : INFINITY;
   }
   if (lane == 0 && a.qstats) a.qstats[q * NR_QSTATS + NR_QS_ROWS] = (int32_t)a.rfull[q];
 }

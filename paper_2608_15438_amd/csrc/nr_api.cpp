@@ -79,7 +79,7 @@ struct Buffers {
   uint32_t *open_q, *open_key;
   uint64_t *open_row;
   int64_t *pool_id, *pool2_id;
-  unsigned long long *counter2;
+  uint32_t *counter2;
   uint32_t *skey;
   int64_t *sid;
   uint32_t *pair_q, *hist, *pair_rank, *slist, *hpos, *lpair, *lpm;
@@ -125,7 +125,7 @@ Buffers carve(char *base, const Shape &s, size_t *bytes) {
   B.tile_off = c.take<int32_t>((size_t)s.nq + 1);
   B.tile_q = c.take<int32_t>((size_t)s.nq * nr::MAX_TILES_PER_QUERY);
   B.tile_c0 = c.take<int32_t>((size_t)s.nq * nr::MAX_TILES_PER_QUERY);
-  B.counter = c.take<int32_t>(1);
+  B.counter = c.take<int32_t>((size_t)nr::TILE_COUNTERS * nr::TILE_COUNTER_STRIDE);
   B.pkey = c.take<uint32_t>((size_t)s.nq * nr::MAX_TILES_PER_QUERY * s.k);
   B.pid = c.take<int64_t>((size_t)s.nq * nr::MAX_TILES_PER_QUERY * s.k);
   B.shared = s.shared;
@@ -141,7 +141,7 @@ Buffers carve(char *base, const Shape &s, size_t *bytes) {
     B.own_rows = c.take<uint32_t>((size_t)s.nq);
     B.scnt = c.take<int32_t>((size_t)s.nq);
     B.flag = c.take<int32_t>((size_t)s.nq);
-    B.counter2 = c.take<unsigned long long>(1);
+    B.counter2 = c.take<uint32_t>((size_t)nr::TILE_COUNTERS * nr::TILE_COUNTER_STRIDE);
     B.skey = c.take<uint32_t>((size_t)s.nq * nr::SURVIVOR_CAP);
     B.sid = c.take<int64_t>((size_t)s.nq * nr::SURVIVOR_CAP);
     B.pool_cnt = c.take<unsigned long long>(1);
@@ -522,6 +522,12 @@ hipError_t run_refine(const nr_index *ix, const void *q, int64_t nq, int k, cons
   pa.rfull = (o.qmask || o.own_cseed) ? nullptr : B.rfull;
   pa.qmask = o.qmask;
   pa.own_cseed = o.own_cseed;
+  // few queries: smaller tiles, so that a query's rows spread over the chip;
+  // with more, a tile's set-up and its partial list cost more than they gain.
+  // Whole searches with tiles of at least 64 / 128 / 256 / 512 rows, us: one
+  // query (756 rows, k = 10) 102 / 105 / 112 / 122; 48 (6,030 rows, k = 10) 127 / 120 / 113 /
+  // 115; 333 (3,700 rows, k = 33) 388 / 260 / 245 / 204
+  pa.tile_min = (uint32_t)std::min<int64_t>(nr::TILE_MIN_ROWS, std::max<int64_t>(64, 8 * nq));
   if (o.own_cseed) {
     pa.clus_out = B.clus_own;
     pa.nclus_out = B.nclus_own;

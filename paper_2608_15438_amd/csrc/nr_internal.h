@@ -68,6 +68,11 @@ constexpr uint32_t SURVIVOR_POOL = NR_SURVIVOR_POOL;  // survivors past SURVIVOR
 #define NR_OPEN_PAIRS (1u << 22)
 #endif
 constexpr uint32_t OPEN_PAIRS = NR_OPEN_PAIRS;  // fp32 rows past 1 KB: pairs open after slab 0
+// The persistent kernels take their tiles from TILE_COUNTERS counters, each in
+// a 128-byte line of its own, a wave always from the same one.  One counter
+// answers an atomic in 12 ns: 8192 waves asking it once took 100 us, however
+// little there was to do.
+constexpr int TILE_COUNTERS = 16, TILE_COUNTER_STRIDE = 32;
 constexpr int SHARED_G = 8;               // queries scored per shared work unit (at most)
 constexpr int SHARED_MAX_NSEG = 48;       // rows of at most 48 x 128 bytes use the shared scan
 constexpr uint32_t SHARED_ROWS = 2048;    // rows per shared work unit (at most)
@@ -206,7 +211,7 @@ struct PlanArgs {
   int32_t *tile_off;     // [nq + 1]
   int32_t *tile_q;       // [nq x MAX_TILES_PER_QUERY]
   int32_t *tile_c0;
-  int32_t *counter;      // work counter of the refinement kernel
+  int32_t *counter;      // [TILE_COUNTERS x TILE_COUNTER_STRIDE] of the refinement kernel
   uint32_t *rfull;       // [nq] rows of the whole list, may be null
   const int32_t *qmask;  // [nq] only queries with qmask[q] != 0 get tiles, may be null
   const int32_t *own_cseed;  // [nq] may be null; else only list positions i < own_cseed[q] count
@@ -309,7 +314,7 @@ struct SharedArgs {
   unsigned long long *open_cnt;  // fp32 rows past 1 KB: (query, row) pairs still at or
   uint32_t *open_q, *open_key;   // before the bound after the first 1 KB slab, their
   uint64_t *open_row;            // running sum and payload row [OPEN_PAIRS]
-  unsigned long long *counter;  // work-unit counter
+  uint32_t *counter;  // [TILE_COUNTERS x TILE_COUNTER_STRIDE] tile counters
   int64_t *wstats;            // [7] scanned rows, seed tiles, scanned pair rows, rows read
                               // past their heads, bytes the scan read from them, row
                               // bytes of the open-pair pass, row bytes of k_refine
@@ -493,22 +498,68 @@ __device__ __forceinline__ uint64_t wave_incl_scan_u64(uint64_t v) {
   }
   return v;
 }
+// the value of lane l ^ M, by VALU moves (DPP inside a row of 16 lanes, row
+// swaps across rows) rather than through the LDS crossbar, whose latency is
+// most of a sorting network's
+template <int M>
+__device__ __forceinline__ uint32_t xor_lane(uint32_t v) {
+  if constexpr (M == 1)
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0xB1, 0xF, 0xF, false);
+  else if constexpr (M == 2)
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x4E, 0xF, 0xF, false);
+  else if constexpr (M == 4) {  // mirror the half row, then each quad: l -> 7 - l -> l ^ 4
+    const int h = __builtin_amdgcn_update_dpp((int)v, (int)v, 0x141, 0xF, 0xF, false);
+    return (uint32_t)__builtin_amdgcn_update_dpp(h, h, 0x1B, 0xF, 0xF, false);
+  } else if constexpr (M == 8)
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, 0x128, 0xF, 0xF, false);
+  else if constexpr (M == 16) {
+    const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    return (lane_id() & 16) ? r[0] : r[1];
+  } else {
+    static_assert(M == 32, "a power of two below 64");
+    const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    return (lane_id() & 32) ? r[0] : r[1];
+  }
+}
+template <int M>
+__device__ __forceinline__ uint64_t xor_lane_u64(uint64_t v) {
+  return ((uint64_t)xor_lane<M>((uint32_t)(v >> 32)) << 32) | xor_lane<M>((uint32_t)v);
+}
+// compare-exchange with lane l ^ J: ascending inside blocks of K lanes whose
+// bit K is clear
+template <int K, int J>
+__device__ __forceinline__ uint64_t sort_step(uint64_t key) {
+  const int l = lane_id();
+  const uint64_t o = xor_lane_u64<J>(key);
+  return (((l & J) == 0) == ((l & K) == 0)) == (key < o) ? key : o;
+}
+template <int K, int J = K / 2>
+__device__ __forceinline__ uint64_t sort_stage(uint64_t key) {
+  key = sort_step<K, J>(key);
+  if constexpr (J > 1) key = sort_stage<K, J / 2>(key);
+  return key;
+}
 // ascending bitonic sort of one u64 key per lane, where every lane from n on
 // holds ~0: only the first power of two >= n lanes need the network
 __device__ __forceinline__ uint64_t wave_sort_u64(uint64_t key, int n = WAVE) {
-  int l = lane_id();
-  int top = 2;
-  while (top < n && top < WAVE) top <<= 1;
-  for (int k = 2; k <= top; k <<= 1) {
-    for (int j = k >> 1; j > 0; j >>= 1) {
-      uint64_t other = shfl_xor_u64(key, j);
-      bool up = (l & k) == 0;
-      bool lower = (l & j) == 0;
-      uint64_t mn = key < other ? key : other, mx = key < other ? other : key;
-      key = (lower == up) ? mn : mx;
-    }
-  }
+  key = sort_stage<2>(key);
+  if (n > 2) key = sort_stage<4>(key);
+  if (n > 4) key = sort_stage<8>(key);
+  if (n > 8) key = sort_stage<16>(key);
+  if (n > 16) key = sort_stage<32>(key);
+  if (n > 32) key = sort_stage<64>(key);
   return key;
+}
+// the 64 least of two ascending lists of 64 keys, ascending
+__device__ __forceinline__ uint64_t wave_merge_least_u64(uint64_t a, uint64_t b) {
+  // b reversed: rows mirrored (l -> l ^ 15), then l ^ 16, l ^ 32
+  uint32_t lo = (uint32_t)b, hi = (uint32_t)(b >> 32);
+  lo = (uint32_t)__builtin_amdgcn_update_dpp((int)lo, (int)lo, 0x140, 0xF, 0xF, false);
+  hi = (uint32_t)__builtin_amdgcn_update_dpp((int)hi, (int)hi, 0x140, 0xF, 0xF, false);
+  lo = xor_lane<32>(xor_lane<16>(lo));
+  hi = xor_lane<32>(xor_lane<16>(hi));
+  const uint64_t r = ((uint64_t)hi << 32) | lo;
+  return sort_stage<64>(a < r ? a : r);
 }
 // number of entries of sorted a[0..n) strictly below key
 __device__ __forceinline__ int lower_bound_u64(const uint64_t *a, int n, uint64_t key) {

@@ -83,3 +83,26 @@ def test_shared_equals_per_query_large_scan():
     both(ix, q, 10, 256, 8, shared_seed_rows=256)
     ix.close()
 
+
+
+@pytest.mark.parametrize("nq", [1, 5, 48, 300, 700])
+@pytest.mark.parametrize("k", [1, 9, 32, 33, 64])
+@pytest.mark.parametrize("dtype,d,n", [("u8", 16, 7001), ("u8", 144, 3000), ("f32", 4, 5000),
+                                       ("f32", 320, 900)])
+def test_ties_order_by_id(nq, k, dtype, d, n):
+    # rows of few values, so that most distances tie: every list is the exact
+    # (distance, id) order, whichever way its entries came in
+    from paper_2608_15438_amd import neuroute as NR
+    ix, rows = make_index(n, d, 4, NR.NR_U8 if dtype == "u8" else NR.NR_F32, 0, seed=nq)
+    g = torch.Generator(device="cuda").manual_seed(k)
+    small = torch.randint(0, 2, (n, d), generator=g, device="cuda")
+    small[: n // 3] = small[0].clone()
+    rows.copy_(small.to(rows.dtype))               # in place: the payload is these rows
+    q = rows[torch.randint(0, n, (nq,), generator=g, device="cuda")].clone()
+    ids, dists = ix.nr_search(q, k, 16, NR.Params(l_sel=4, r_max=4, k_c=64, shared_seed_rows=64))
+    rid = ix.dev[1]
+    dist = torch.cdist(q.double(), rows.double()).square().round()   # whole numbers
+    key, at = (dist * (1 << 20) + rid).sort(dim=1)
+    assert torch.equal(ids, rid[at[:, :k]])
+    assert torch.equal(dists.double(), dist.gather(1, at[:, :k]))
+    ix.close()
