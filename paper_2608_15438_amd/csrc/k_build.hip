@@ -481,27 +481,6 @@ __device__ __forceinline__ double sqd(const float (&x)[BP], const float (&c)[BP]
   return acc;
 }
 
-// inclusive scan over the wave of values below 2^26, by DPP moves (rows of 16
-// lanes, then row totals onto the rows after them)
-__device__ __forceinline__ uint32_t dpp_incl_scan(uint32_t v) {
-  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, false);  // row_shr:1
-  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, false);
-  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, false);
-  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, false);
-  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false);  // row_bcast:15
-  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false);  // row_bcast:31
-  return v;
-}
-
-// inclusive scan of weights of at most 2^30 each, as two halves of 15 bits
-// (the shuffles of a 64-bit scan take ten times as long, and every draw of the
-// k-means++ waits for one)
-__device__ __forceinline__ int64_t weight_incl_scan(int64_t w) {
-  const uint32_t lo = dpp_incl_scan((uint32_t)w & 0x7FFFu);
-  const uint32_t hi = dpp_incl_scan((uint32_t)w >> 15);
-  return ((int64_t)hi << 15) + (int64_t)lo;
-}
-
 // k-means++ of a bucket of at most 64 rows by one wave, a sample member per
 // lane: its row and D^2 stay in registers, the running weights are a wave scan
 template <int BP>
@@ -531,7 +510,7 @@ __global__ void __launch_bounds__(BT) k_build_seed_wave(KmArgs a, SizeLists l) {
   for (int r = 0; r < K; ++r) {
     if (r > 0) {
       const int64_t w = lane < S ? d2_weight(d2) : 0;
-      const int64_t incl = weight_incl_scan(w);
+      const int64_t incl = (int64_t)wave_incl_scan_u64((uint64_t)w);
       const int64_t tot = (int64_t)bcast_u64((uint64_t)incl, WAVE - 1);
       int pick = 0;
       if (tot > 0) {
@@ -614,8 +593,7 @@ __global__ void __launch_bounds__(NT) k_build_seed_list(KmArgs a, const uint32_t
       if ((r & (WAVE - 1)) == 0) us = r + lane < K ? U[r + lane] : 0.0;
       if (r > 0) {
         const int p = r & 1;
-        const int64_t incl = per == 1 ? weight_incl_scan(wsum)
-                                      : (int64_t)wave_incl_scan_u64((uint64_t)wsum);
+        const int64_t incl = (int64_t)wave_incl_scan_u64((uint64_t)wsum);
         if (lane == WAVE - 1) s_tot[p][wv] = incl;
         __syncthreads();
         if (threadIdx.x == 0) s_pick[p ^ 1] = S;   // read by all before this barrier

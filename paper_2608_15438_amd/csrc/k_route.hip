@@ -445,7 +445,89 @@ __device__ __forceinline__ void route_query(const RouteArgs &a, const int64_t q)
     __builtin_amdgcn_wave_barrier();
   };
 
-  if (!a.finite) {
+  // While fewer than K_c keys pass the gate, H never fills, the stop cannot
+  // fire, and (theta never rises) what the batches keep is what the last theta
+  // keeps.  Such a query's clusters are scored 64 at a time, whatever buckets
+  // and bins they come from, and gated by the last theta; the batches' chain
+  // -- minimum, margin, gate, append, counts -- is left to the queries whose
+  // heap can fill, and to those that report their batches.  Keys at or below
+  // the theta of the chunks before bound the batches' count from above; a
+  // query whose bound reaches K_c starts again batch by batch, so queries with
+  // more than three times K_c clusters do not try.  One query of 1M x 128 (313
+  // clusters scored in 26 batches) 45 -> 11 us.
+  bool direct = false, all_fit = false;
+  if (!a.qstats) {
+    uint32_t ms = 0;
+    for (int i = lane; i < cnt; i += WAVE) {
+      const uint2 r = i < nst ? make_uint2(st_c0[i], st_c1[i]) : lk[i];
+      const uint32_t sz = r.y - r.x;
+      ms += sz >= 2 ? sz : 0u;
+    }
+    ms = wave_sum_u32(ms);
+    all_fit = ms <= (uint32_t)hcap &&
+              (a.early_stop_on ? ms < (uint32_t)k_c : ms <= (uint32_t)k_c);
+    direct = all_fit || ms <= 3u * (uint32_t)k_c;
+  }
+  if (direct) {
+    const int room = hcap < k_c - 1 ? hcap : k_c - 1;
+    int bound = 0;             // at least the keys the batches would keep
+    float theta = INFINITY;    // after the chunks so far
+    for (p = 0; p < cnt && direct; p += WAVE) {
+      load_window();
+      const int lim = cnt - p < WAVE ? cnt - p : WAVE;
+      const uint32_t c0 = S.wc0[lane];
+      const uint32_t sz = lane < lim ? S.wc1[lane] - c0 : 0u;
+      const uint64_t sm = ballot(sz == 1);
+      if (sz == 1) out[ndir + popc64(sm & lanemask_lt())] = c0;
+      ndir += popc64(sm);
+      const uint32_t msz = sz >= 2 ? sz : 0u;
+      const uint32_t incl = wave_incl_scan_u32(msz);
+      const int total = (int)bcast_u32(incl, WAVE - 1);
+      S.wpre[lane] = incl - msz;
+      __builtin_amdgcn_wave_barrier();
+      for (int from = 0; from < total; from += WAVE) {
+        const bool in = from + lane < total;
+        const uint32_t num = (uint32_t)(in ? from + lane : from);
+        int lo = 0, hi = lim - 1;  // the last slot whose prefix is <= num
+        while (lo < hi) {
+          const int mid = (lo + hi + 1) >> 1;
+          if (S.wpre[mid] <= num) lo = mid; else hi = mid - 1;
+        }
+        const uint32_t cid = S.wc0[lo] + (num - S.wpre[lo]);
+        const float d = centroid_dist(cid);
+        bound += popc64(ballot(in && d <= theta));
+        if (!all_fit && bound > room) {
+          direct = false;
+          break;
+        }
+        const float dm = route_min_f32(in ? d : INFINITY);
+        d_min = dm < d_min ? dm : d_min;
+        if (a.gate_on) theta = d_min + margin_dev(a.m_knots, kx, ky, ks, d_min);
+        const bool keep = in && d <= theta;
+        const uint64_t km = ballot(keep);
+        if (keep) H[npool + popc64(km & lanemask_lt())] = ((uint64_t)__float_as_uint(d) << 32) | cid;
+        npool += popc64(km);
+      }
+      __builtin_amdgcn_wave_barrier();
+    }
+    cut_last = ((uint64_t)__float_as_uint(theta) + 1ull) << 32;
+    if (!direct) {  // the heap could fill: from the start, batch by batch
+      npool = ndir = p = 0;
+      d_min = INFINITY;
+      have_window = false;
+      cut_last = ~0ull;
+    } else if (a.unordered) {  // the caller takes H's clusters in any order
+      for (int i0 = 0; i0 < npool; i0 += WAVE) {
+        const uint64_t key = i0 + lane < npool ? H[i0 + lane] : ~0ull;
+        const uint64_t keep = ballot(key < cut_last);
+        if (key < cut_last) out[ndir + popc64(keep & lanemask_lt())] = (uint32_t)key;
+        ndir += popc64(keep);
+      }
+      npool = 0;
+      fastm = false;
+    }
+  }
+  if (!direct && !a.finite) {
     // S_max = +inf: every probe is its own bin.  Runs of bins without a
     // multi-cluster bucket change neither H nor t_low, so they are taken a
     // window at a time; the stop test after each of them can only fire
@@ -509,7 +591,7 @@ __device__ __forceinline__ void route_query(const RouteArgs &a, const int64_t q)
         p += 1;
       }
     }
-  } else {
+  } else if (!direct) {
     for (int z = 0; z <= z_last && !stop; ++z) {
       b_proc += 1;
       while (p < cnt) {

@@ -449,7 +449,7 @@ hipError_t run_probe(const nr_index *ix, const float *logits, int64_t nq, int P,
 hipError_t run_route(const nr_index *ix, const float *logits, int64_t nq, int P,
                      const nr_params *p, const Buffers &B, uint32_t *clus, int32_t *nclus,
                      int64_t cap, int32_t *qstats, hipStream_t s,
-                     const nr::PairHistArgs *ph = nullptr) {
+                     const nr::PairHistArgs *ph = nullptr, bool unordered = false) {
   nr::RouteArgs a{};
   a.logits = logits;
   a.nq = nq;
@@ -482,6 +482,7 @@ hipError_t run_route(const nr_index *ix, const float *logits, int64_t nq, int P,
   a.nclus = nclus;
   a.cap = cap;
   a.qstats = qstats;
+  a.unordered = unordered;
   if (ph) {
     a.ph = *ph;
     a.ph_on = 1;
@@ -1069,8 +1070,9 @@ nr_status nr_search_ex(const nr_index *cix, const void *queries, const float *lo
       HIP_OK(nr::launch_shared_hist(sa, w->clean_hist != B.hist, stream));
       w->clean_hist = nullptr;
     }
+    // refined query by query, a list's order is of no consequence
     HIP_OK(run_route(ix, lg, n, P, p, B, B.clus, B.nclus, cap, qs, stream,
-                     B.shared ? &ph : nullptr));
+                     B.shared ? &ph : nullptr, !B.shared));
     if (prof) HIP_OK(hipEventRecord(es.ev[3], stream));
     if (B.shared) {
       HIP_OK(run_refine_shared(ix, sa, qp, n, k, B.clus, B.nclus, cap, B, out_ids + q0 * k,
@@ -1138,7 +1140,7 @@ nr_status nr_search_noalloc(const nr_index *cix, const void *queries, const floa
     const float *lg = logits ? logits + q0 * ix->d.b : B.logits;
     if (!logits) HIP_OK(run_encode(ix, qp, n, B.logits, B, stream));
     HIP_OK(run_probe(ix, lg, n, P, p, B.codes, B.costs, B.bins, B.counts, stream, &B));
-    HIP_OK(run_route(ix, lg, n, P, p, B, B.clus, B.nclus, cap, nullptr, stream));
+    HIP_OK(run_route(ix, lg, n, P, p, B, B.clus, B.nclus, cap, nullptr, stream, nullptr, true));
     HIP_OK(run_refine(ix, qp, n, k, B.clus, B.nclus, cap, B, out_ids + q0 * k,
                       out_dists + q0 * k, nullptr, stream, nullptr));
   }

@@ -193,6 +193,7 @@ struct RouteArgs {
   int32_t *nclus;        // [nq]
   int64_t cap;
   int32_t *qstats;       // [nq x NR_QSTATS] or null
+  int unordered;         // the order of H's clusters in the list does not matter
   PairHistArgs ph;       // with ph_on: each query's pairs are counted once its list is final
   int ph_on;
 };
@@ -477,26 +478,38 @@ __device__ __forceinline__ float wave_min_f32(float v) {
   for (int m = 32; m >= 1; m >>= 1) v = fminf(v, __shfl_xor(v, m));
   return v;
 }
-__device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v) {
-  for (int m = 32; m >= 1; m >>= 1) v += (uint32_t)__shfl_xor((int)v, m);
+// inclusive scans over the wave by DPP moves (shifts inside rows of 16 lanes,
+// then row totals onto the rows after them; lanes a move leaves out add 0):
+// six dependent VALU steps where shuffles wait for the LDS crossbar six times
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_or_zero(uint32_t v) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xF, false);
+}
+__device__ __forceinline__ uint32_t wave_incl_scan_u32(uint32_t v) {
+  v += dpp_or_zero<0x111, 0xF>(v);  // row_shr:1, 2, 4, 8
+  v += dpp_or_zero<0x112, 0xF>(v);
+  v += dpp_or_zero<0x114, 0xF>(v);
+  v += dpp_or_zero<0x118, 0xF>(v);
+  v += dpp_or_zero<0x142, 0xA>(v);  // row_bcast:15 onto rows 1 and 3
+  v += dpp_or_zero<0x143, 0xC>(v);  // row_bcast:31 onto rows 2 and 3
   return v;
 }
-// inclusive scan over the wave (u32)
-__device__ __forceinline__ uint32_t wave_incl_scan_u32(uint32_t v) {
-  int l = lane_id();
-  for (int o = 1; o < WAVE; o <<= 1) {
-    uint32_t t = (uint32_t)__shfl_up((int)v, o);
-    if (l >= o) v += t;
-  }
-  return v;
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint64_t dpp_or_zero_u64(uint64_t v) {
+  return ((uint64_t)dpp_or_zero<CTRL, ROWS>((uint32_t)(v >> 32)) << 32) |
+         dpp_or_zero<CTRL, ROWS>((uint32_t)v);
 }
 __device__ __forceinline__ uint64_t wave_incl_scan_u64(uint64_t v) {
-  int l = lane_id();
-  for (int o = 1; o < WAVE; o <<= 1) {
-    uint64_t t = shfl_up_u64(v, o);
-    if (l >= o) v += t;
-  }
+  v += dpp_or_zero_u64<0x111, 0xF>(v);
+  v += dpp_or_zero_u64<0x112, 0xF>(v);
+  v += dpp_or_zero_u64<0x114, 0xF>(v);
+  v += dpp_or_zero_u64<0x118, 0xF>(v);
+  v += dpp_or_zero_u64<0x142, 0xA>(v);
+  v += dpp_or_zero_u64<0x143, 0xC>(v);
   return v;
+}
+__device__ __forceinline__ uint32_t wave_sum_u32(uint32_t v) {
+  return bcast_u32(wave_incl_scan_u32(v), WAVE - 1);
 }
 // the value of lane l ^ M, by VALU moves (DPP inside a row of 16 lanes, row
 // swaps across rows) rather than through the LDS crossbar, whose latency is

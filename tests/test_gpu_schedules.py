@@ -9,9 +9,9 @@ torch = pytest.importorskip("torch")
 pytestmark = pytest.mark.gpu
 
 
-def make_index(n, d, b, dtype, head, seed=0):
-    """Random rows in random buckets, one cluster per non-empty bucket; the
-    latents are d -> b random projections."""
+def make_index(n, d, b, dtype, head, seed=0, per=1):
+    """Random rows in random buckets, up to `per` clusters in each; the latents
+    are d -> b random projections."""
     from paper_2608_15438_amd import neuroute as NR
     g = torch.Generator(device="cuda").manual_seed(seed)
     rng = np.random.default_rng(seed)
@@ -20,8 +20,10 @@ def make_index(n, d, b, dtype, head, seed=0):
     else:
         rows = torch.randn((n, d), generator=g, device="cuda")
     sizes = np.bincount(rng.integers(0, 1 << b, n), minlength=1 << b)
-    nz = sizes[sizes > 0]
-    bc = np.concatenate([[0], np.cumsum(sizes > 0)])
+    k = np.minimum(sizes, rng.integers(1, per + 1, 1 << b))  # clusters of each bucket
+    nz = np.concatenate([[s // c + (i < s % c) for i in range(c)] for s, c in zip(sizes, k)])
+    nz = nz.astype(np.int64)
+    bc = np.concatenate([[0], np.cumsum(k)])
     cl = np.concatenate([[0], np.cumsum(nz)])
     raw = rows.view(torch.uint8)
     pay = torch.cat([raw[:, :head].reshape(-1), raw.reshape(-1)]) if head else raw.reshape(-1)
@@ -105,4 +107,27 @@ def test_ties_order_by_id(nq, k, dtype, d, n):
     key, at = (dist * (1 << 20) + rid).sort(dim=1)
     assert torch.equal(ids, rid[at[:, :k]])
     assert torch.equal(dists.double(), dist.gather(1, at[:, :k]))
+    ix.close()
+
+
+@pytest.mark.parametrize("b,per,P,s_max", [(6, 9, 64, 0.0), (7, 3, 40, 0.0), (6, 30, 64, 4.0),
+                                           (5, 1, 32, 0.0), (9, 80, 300, 0.0)])
+@pytest.mark.parametrize("nq", [33, 600])
+def test_one_gate_equals_batches(b, per, P, s_max, nq):
+    # queries whose heap cannot fill are gated once, those that report their
+    # counters go batch by batch: the same lists, around the K_c where the two part
+    from paper_2608_15438_amd import neuroute as NR
+    ix, rows = make_index(20_000, 16, b, NR.NR_F32, 0, seed=b, per=per)
+    q = rows[:nq].clone()
+    kw = dict(l_sel=b, r_max=b, m_x=[0.0, 4.0], m_y=[1.0, 3.0], shared_seed_rows=64)
+    if s_max:
+        kw.update(s_max=s_max, n_bins=8)
+    stats = ix.nr_search(q, 10, P, NR.Params(k_c=16000, **kw), qstats=True)[2]
+    scored = sorted(set(stats[:, 3].tolist()))
+    for kc in {1, 64, 512, 600, 2100} | {max(1, scored[len(scored) // 2] + o) for o in (-1, 0, 1)}:
+        for stop in (True, False):
+            p = NR.Params(k_c=kc, early_stop_on=stop, **kw)
+            a = ix.nr_search(q, 10, P, p)
+            r = ix.nr_search(q, 10, P, p, qstats=True)
+            assert torch.equal(a[0], r[0]) and torch.equal(a[1], r[1]), (kc, stop)
     ix.close()
