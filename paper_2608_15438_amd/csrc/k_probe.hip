@@ -29,6 +29,10 @@ __global__ void __launch_bounds__(64) k_probe(ProbeArgs a) {
   const int lane = lane_id();
   const int64_t q = blockIdx.x;
   if (q >= a.nq) return;
+  if (lane < 2 && a.zero.per_query[lane]) a.zero.per_query[lane][q] = 0;
+  if (q == 0)
+    for (int z = 0; z < 6; ++z)
+      for (int i = lane; i < a.zero.n[z]; i += WAVE) a.zero.p[z][i] = 0;
   const int P = a.P, b = a.b, l_sel = a.l_sel;
   const int pc = (P + WAVE - 1) / WAVE * WAVE;
   uint64_t *L = reinterpret_cast<uint64_t *>(smem_raw);

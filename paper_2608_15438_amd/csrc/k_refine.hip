@@ -2,8 +2,8 @@
 // Sec. 3.5) -- the HBM-bound part of the search.
 //
 //  plan   (one wave per query)  row prefix over the query's clusters, total
-//         rows R_q, tile size T_q = max(TILE_MIN_ROWS, ceil(R_q / 64)), then
-//         a scan over queries numbers the (query, row range) tiles;
+//         rows R_q, tile size T_q = max(smallest, ceil(R_q / 64)) and the
+//         (query, row range) tiles;
 //  refine (persistent waves)    each wave takes tiles from an atomic counter
 //         and walks the tile's virtual rows; 8 lanes cover one 128-byte row
 //         segment with one 16-byte load each, so a wave instruction reads 8
@@ -49,122 +49,105 @@ __device__ __forceinline__ int clamp_count(int32_t n, int64_t cap) {
   return n < 0 ? 0 : (n > cap ? (int)cap : n);
 }
 
-__global__ void __launch_bounds__(256) k_plan_rows(PlanArgs a) {
-  const int lane = lane_id();
-  const int64_t q = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-  if (q >= a.nq) return;
-  if (a.qmask && !a.qmask[q]) {
-    if (lane == 0) {
-      a.rtot[q] = 0;
-      a.tsize[q] = TILE_MIN_ROWS;
-      a.ntile[q] = 0;
-    }
-    return;
-  }
-  const int n = clamp_count(a.nclus[q], a.cap);
-  const uint32_t *cl = a.clus + q * a.cap;
-  uint32_t *pre = a.rowpre + q * (a.cap + 1);
-  uint64_t run = 0;
-  const int own0 = a.own_cseed ? a.own_cseed[q] : 0;
-  // own (seed) pass of the shared schedule: only the leading clusters, compacted
-  uint32_t *co = a.clus_out ? a.clus_out + q * a.cap : nullptr;
-  int nout = 0;
-  if (lane == 0) pre[0] = 0;
-  // the compacted seed pass needs only the leading clusters
-  const int nw = co && a.own_cseed && own0 < n ? own0 : n;
-  for (int i0 = 0; i0 < nw; i0 += WAVE) {
-    const int i = i0 + lane;
-    uint32_t c = 0;
-    uint64_t sz = 0;
-    if (i < nw) {
-      c = cl[i];
-      if (c < a.n_clusters) {
-        sz = a.cl_off[(uint64_t)c + 1] - a.cl_off[c];
-        // the seed pass leaves every later cluster to the scan
-        if (a.own_cseed && i >= own0) sz = 0;
+// One wave per query: the rows before each of its clusters, its tile size, its
+// tiles (numbered from one atomic per block, so in any order: the merge orders
+// the results) and each tile's first cluster.  (As three kernels -- rows, a
+// scan over the queries, tiles -- 14 us for one query, 35 for 10,000.)
+constexpr int PLAN_WAVES = 16;
+__global__ void __launch_bounds__(PLAN_WAVES * WAVE) k_plan(PlanArgs a) {
+  __shared__ int32_t s_nt[PLAN_WAVES];
+  __shared__ int32_t s_base;
+  const int lane = lane_id(), wv = threadIdx.x / WAVE;
+  const int64_t q = (int64_t)blockIdx.x * PLAN_WAVES + wv;
+  const bool live = q < a.nq && !(a.qmask && !a.qmask[q]);
+  uint32_t *pre = a.rowpre + (live ? q : 0) * (a.cap + 1);
+  uint32_t tot = 0, t = TILE_MIN_ROWS;
+  int nt = 0, ncl = 0;
+  if (live) {
+    const int n = clamp_count(a.nclus[q], a.cap);
+    const uint32_t *cl = a.clus + q * a.cap;
+    uint64_t run = 0;
+    const int own0 = a.own_cseed ? a.own_cseed[q] : 0;
+    // own (seed) pass of the shared schedule: only the leading clusters, compacted
+    uint32_t *co = a.clus_out ? a.clus_out + q * a.cap : nullptr;
+    int nout = 0;
+    if (lane == 0) pre[0] = 0;
+    // the compacted seed pass needs only the leading clusters
+    const int nw = co && a.own_cseed && own0 < n ? own0 : n;
+    for (int i0 = 0; i0 < nw; i0 += WAVE) {
+      const int i = i0 + lane;
+      uint32_t c = 0;
+      uint64_t sz = 0;
+      if (i < nw) {
+        c = cl[i];
+        if (c < a.n_clusters) {
+          sz = a.cl_off[(uint64_t)c + 1] - a.cl_off[c];
+          // the seed pass leaves every later cluster to the scan
+          if (a.own_cseed && i >= own0) sz = 0;
+        }
       }
-    }
-    const uint64_t incl = wave_incl_scan_u64(sz);
-    if (co) {
-      const uint64_t keep = ballot(sz > 0);
-      const int pos = nout + popc64(keep & lanemask_lt());
-      if (sz > 0) {
-        co[pos] = c;
-        pre[pos + 1] = (uint32_t)(run + incl);
+      const uint64_t incl = wave_incl_scan_u64(sz);
+      if (co) {
+        const uint64_t keep = ballot(sz > 0);
+        const int pos = nout + popc64(keep & lanemask_lt());
+        if (sz > 0) {
+          co[pos] = c;
+          pre[pos + 1] = (uint32_t)(run + incl);
+        }
+        nout += popc64(keep);
+      } else if (i < n) {
+        pre[i + 1] = (uint32_t)(run + incl);
       }
-      nout += popc64(keep);
-    } else if (i < n) {
-      pre[i + 1] = (uint32_t)(run + incl);
+      run += bcast_u64(incl, WAVE - 1);
     }
-    run += bcast_u64(incl, WAVE - 1);
-  }
-  if (lane == 0) {
+    ncl = co ? nout : n;
     // a list of more than 2^32 - 1 rows (only possible with repeated clusters
     // given to nr_refine) is refused: it returns no candidates
-    const uint32_t tot = run > 0xffffffffull ? 0u : (uint32_t)run;
+    tot = run > 0xffffffffull ? 0u : (uint32_t)run;
     const uint32_t tmin = a.tile_min ? a.tile_min : TILE_MIN_ROWS;
-    uint32_t t = (tot + MAX_TILES_PER_QUERY - 1) / MAX_TILES_PER_QUERY;
+    t = (tot + MAX_TILES_PER_QUERY - 1) / MAX_TILES_PER_QUERY;
     if (t < tmin) t = tmin;
+    nt = (int)(((uint64_t)tot + t - 1) / t);
+    if (lane == 0) {
+      if (a.rfull) a.rfull[q] = tot;
+      if (co) a.nclus_out[q] = nout;
+    }
+  }
+  if (lane == 0) s_nt[wv] = nt;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int32_t sum = 0;
+    for (int i = 0; i < PLAN_WAVES; ++i) sum += s_nt[i];
+    s_base = sum > 0 ? atomicAdd(&a.tile_off[a.nq], sum) : 0;
+  }
+  __syncthreads();
+  if (q >= a.nq) return;
+  int32_t off = s_base;
+  for (int i = 0; i < wv; ++i) off += s_nt[i];
+  if (lane == 0) {
     a.rtot[q] = tot;
     a.tsize[q] = t;
-    a.ntile[q] = (int32_t)(((uint64_t)tot + t - 1) / t);
-    if (a.rfull) a.rfull[q] = tot;
-    if (co) a.nclus_out[q] = nout;
+    a.ntile[q] = nt;
+    a.tile_off[q] = off;
   }
-}
-
-// exclusive scan of ntile over all queries in one block; resets the counter
-__global__ void __launch_bounds__(1024) k_plan_scan(PlanArgs a) {
-  __shared__ int32_t part[1024];
-  const int tid = threadIdx.x;
-  const int64_t per = (a.nq + 1023) / 1024;
-  const int64_t s0 = tid * per;
-  int32_t sum = 0;
-  for (int64_t i = s0; i < s0 + per && i < a.nq; ++i) sum += a.ntile[i];
-  part[tid] = sum;
-  __syncthreads();
-  for (int o = 1; o < 1024; o <<= 1) {
-    int32_t v = tid >= o ? part[tid - o] : 0;
-    __syncthreads();
-    part[tid] += v;
-    __syncthreads();
+  __threadfence_block();  // the wave reads back the row prefix it wrote
+  for (int x = lane; x < nt; x += WAVE) {
+    const uint32_t v0 = (uint32_t)x * t;
+    // last cluster i with pre[i] <= v0 (clusters of zero rows are skipped)
+    int lo = 0, hi = ncl - 1;
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) >> 1;
+      if (pre[mid] <= v0) lo = mid; else hi = mid - 1;
+    }
+    a.tile_q[off + x] = (int32_t)q;
+    a.tile_c0[off + x] = lo;
   }
-  int32_t run = part[tid] - sum;
-  for (int64_t i = s0; i < s0 + per && i < a.nq; ++i) {
-    a.tile_off[i] = run;
-    run += a.ntile[i];
-  }
-  if (tid == 1023) {
-    a.tile_off[a.nq] = part[1023];
-  }
-  if (tid < TILE_COUNTERS) a.counter[tid * TILE_COUNTER_STRIDE] = 0;
-}
-
-// one thread per (query, tile slot): tile -> query and first cluster
-__global__ void __launch_bounds__(256) k_plan_tiles(PlanArgs a) {
-  const int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t q = g / MAX_TILES_PER_QUERY;
-  const int t = (int)(g % MAX_TILES_PER_QUERY);
-  if (q >= a.nq || t >= a.ntile[q]) return;
-  const int32_t tix = a.tile_off[q] + t;
-  const uint32_t v0 = (uint32_t)t * a.tsize[q];
-  const uint32_t *pre = a.rowpre + q * (a.cap + 1);
-  // last cluster i with pre[i] <= v0 (clusters of zero rows are skipped)
-  int lo = 0, hi = clamp_count(a.clus_out ? a.nclus_out[q] : a.nclus[q], a.cap) - 1;
-  while (lo < hi) {
-    int mid = (lo + hi + 1) >> 1;
-    if (pre[mid] <= v0) lo = mid; else hi = mid - 1;
-  }
-  a.tile_q[tix] = (int32_t)q;
-  a.tile_c0[tix] = lo;
 }
 
 hipError_t launch_plan(const PlanArgs &a, hipStream_t s) {
   if (a.nq <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_plan_rows, dim3((unsigned)((a.nq + 3) / 4)), dim3(256), 0, s, a);
-  hipLaunchKernelGGL(k_plan_scan, dim3(1), dim3(1024), 0, s, a);
-  int64_t th = a.nq * MAX_TILES_PER_QUERY;
-  hipLaunchKernelGGL(k_plan_tiles, dim3((unsigned)((th + 255) / 256)), dim3(256), 0, s, a);
+  hipLaunchKernelGGL(k_plan, dim3((unsigned)((a.nq + PLAN_WAVES - 1) / PLAN_WAVES)),
+                     dim3(PLAN_WAVES * WAVE), 0, s, a);
   return hipGetLastError();
 }
 
@@ -698,7 +681,7 @@ __global__ void __launch_bounds__(256) k_merge(MergeArgs a) {
   if (q >= a.nq) return;
   if (a.qmask && !a.qmask[q]) return;
   const int k = a.k;
-  const int64_t e0 = (int64_t)a.tile_off[q] * k, e1 = (int64_t)a.tile_off[q + 1] * k;
+  const int64_t e0 = (int64_t)a.tile_off[q] * k, e1 = e0 + (int64_t)a.ntile[q] * k;
   // (key, id) in one word (ids are below 2^32, -1 is an empty entry).  The
   // tiles' lists are sorted; those of as many tiles as fit 64 lanes are sorted
   // together, then merged with the best so far
@@ -721,9 +704,29 @@ __global__ void __launch_bounds__(256) k_merge(MergeArgs a) {
     a.out_dists[q * k + lane] =
         have ? (a.is_u8 ? (float)key : __uint_as_float(key)) : INFINITY;
   }
+  // The scan's record of the query: its bound (the k-th key of the seed pass,
+  // or all ones while that list is short), the bound the head test compares
+  // with, and |q|^2 for uint8 rows.  uint8 keys are integers, so the head bound
+  // is the key minus |q head|^2 (a row's head part of the distance is |x_h|^2 -
+  // 2 x_h.q_h + |q_h|^2); fp32 rows keep a relative margin of 1e-4 over the key
+  // for the rounding of the head's partial sum.
+  if (a.qrec && lane == k - 1) {
+    const uint32_t bound = (uint32_t)(best >> 32);   // an empty entry's is all ones
+    uint4 r = make_uint4(bound, 0u, 0u, 0u);
+    if (a.is_u8) {
+      const uint2 qn = a.qnorm[q];
+      r.y = (uint32_t)(bound == 0xffffffffu ? INT32_MAX
+                                            : (int32_t)((int64_t)bound - (int64_t)qn.y));
+      r.z = qn.x;
+    } else {
+      r.y = bound == 0xffffffffu ? __float_as_uint(INFINITY)
+                                 : __float_as_uint(__uint_as_float(bound) * 1.0001f);
+    }
+    a.qrec[q] = r;
+  }
   if (lane == 0 && a.qstats) {
     a.qstats[q * NR_QSTATS + NR_QS_ROWS] = (int32_t)a.rtot[q];
-    a.qstats[q * NR_QSTATS + NR_QS_TILES] = a.tile_off[q + 1] - a.tile_off[q];
+    a.qstats[q * NR_QSTATS + NR_QS_TILES] = a.ntile[q];
   }
 }
 

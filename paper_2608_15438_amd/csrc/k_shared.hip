@@ -365,14 +365,6 @@ __global__ void __launch_bounds__(256) k_pair_scatter(SharedArgs a) {
 }
 
 hipError_t launch_shared_prep(const SharedArgs &a, hipStream_t s) {
-  hipError_t e = launch_fill_i32(a.scnt, a.nq, 0, s);
-  if (e == hipSuccess) e = launch_fill_i32(a.flag, a.nq, 0, s);
-  if (e == hipSuccess) e = launch_fill_i32((int32_t *)(a.wstats + 3), 6, 0, s);
-  if (e == hipSuccess) e = launch_fill_i32((int32_t *)a.pool_cnt, 2, 0, s);
-  if (e == hipSuccess) e = launch_fill_i32((int32_t *)a.open_cnt, 2, 0, s);
-  if (e == hipSuccess)
-    e = launch_fill_i32((int32_t *)a.counter, TILE_COUNTERS * TILE_COUNTER_STRIDE, 0, s);
-  if (e != hipSuccess) return e;
   const int64_t nblk = list_blocks(a.n_clusters);
   hipLaunchKernelGGL(k_list_count, dim3((unsigned)nblk), dim3(LIST_THREADS), 0, s, a);
   hipLaunchKernelGGL(k_list_scan, dim3(1), dim3(LIST_THREADS), 0, s, a, nblk);
@@ -1109,37 +1101,6 @@ __global__ void __launch_bounds__(256, NSEG <= 1 ? NR_SCAN_WAVES1 : (NSEG > 8 ? 
   if (lane == 0 && body_bytes) atomicAdd((unsigned long long *)&a.wstats[4], body_bytes);
 }
 
-// The scan's record of each query, one thread per query, once the seed merge
-// has written the query's own top-k: its bound (the k-th key of the seed
-// pass, or all ones while that list is short), the bound the head test
-// compares with, and |q|^2 for uint8 rows.  uint8 keys are integers, so the
-// head bound is the key minus |q head|^2 (a row's head part of the distance
-// is |x_h|^2 - 2 x_h.q_h + |q_h|^2); fp32 rows keep a relative margin of 1e-4
-// over the key for the rounding of the head's partial sum.
-__global__ void __launch_bounds__(256) k_scan_qrec(SharedArgs a) {
-  const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (q >= a.nq) return;
-  const int k = a.k;
-  const int64_t own_id = a.own_ids[q * k + k - 1];
-  const float own_d = a.own_dists[q * k + k - 1];
-  const uint32_t bound =
-      own_id < 0 ? 0xffffffffu : (a.is_u8 ? (uint32_t)own_d : __float_as_uint(own_d));
-  uint4 r;
-  r.x = bound;
-  r.w = 0;
-  if (a.is_u8) {
-    const uint2 qn = a.qnorm[q];
-    r.y = (uint32_t)(bound == 0xffffffffu ? INT32_MAX
-                                          : (int32_t)((int64_t)bound - (int64_t)qn.y));
-    r.z = qn.x;
-  } else {
-    r.y = bound == 0xffffffffu ? __float_as_uint(INFINITY)
-                               : __float_as_uint(__uint_as_float(bound) * 1.0001f);
-    r.z = 0;
-  }
-  a.qrec[q] = r;
-}
-
 template <int IS_U8, int NSEG>
 static hipError_t launch_scan_h(const SharedArgs &a, int hl, int grid, hipStream_t s) {
   switch (hl) {
@@ -1169,9 +1130,6 @@ hipError_t launch_shared_refine(const SharedArgs &a, int dtype, int n_cu, hipStr
   const int hl = a.scan_head / 16;
   if (nseg > SHARED_MAX_NSEG || a.scan_head % 16 != 0 || a.scan_head > a.row_bytes)
     return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_scan_qrec, dim3((unsigned)((a.nq + 255) / 256)), dim3(256), 0, s, a);
-  const hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
   const int grid = n_cu * NR_SHARED_BLOCKS_PER_CU;
   return dtype == NR_U8 ? launch_scan_t<1>(a, nseg, hl, grid, s)
                         : launch_scan_t<0>(a, nseg, hl, grid, s);
@@ -1242,6 +1200,7 @@ hipError_t launch_scan_open(const SharedArgs &a, int dtype, int n_cu, hipStream_
 __global__ void __launch_bounds__(1024) k_pool_offsets(SharedArgs a) {
   __shared__ uint32_t part[1024];
   const int tid = threadIdx.x;
+  if (*a.pool_cnt == 0) return;  // no query reads its offset
   const int64_t per = (a.nq + 1023) / 1024;
   const int64_t s0 = tid * per;
   uint32_t sum = 0;
@@ -1306,8 +1265,12 @@ __global__ void __launch_bounds__(256) k_shared_merge(SharedArgs a) {
   if (q >= a.nq) return;
   if (lane == 0) {
     a.own_rows[q] = a.rtot[q];
-    if (q == 0) a.wstats[1] = a.tile_off[a.nq];
+    if (q == 0) {
+      a.wstats[1] = a.tile_off[a.nq];
+      a.tile_off[a.nq] = 0;   // for the plan of the flagged queries
+    }
   }
+  if (q == 0 && lane < TILE_COUNTERS) a.own_counter[lane * TILE_COUNTER_STRIDE] = 0;
   const int k = a.k;
   if (a.flag[q]) return;  // a survivor was lost: recomputed by the per-query schedule
   const int cnt = a.scnt[q];

@@ -414,8 +414,10 @@ hipError_t run_encode(const nr_index *ix, const void *q, int64_t nq, float *logi
 // looked_up = true) on the same buffers
 hipError_t run_probe(const nr_index *ix, const float *logits, int64_t nq, int P,
                      const nr_params *p, uint32_t *codes, float *costs, int32_t *bins,
-                     int32_t *counts, hipStream_t s, const Buffers *route = nullptr) {
+                     int32_t *counts, hipStream_t s, const Buffers *route = nullptr,
+                     const nr::ZeroArgs *zero = nullptr) {
   nr::ProbeArgs a{};
+  if (zero) a.zero = *zero;
   a.logits = logits;
   a.tau = ix->tau;
   a.nq = nq;
@@ -443,6 +445,30 @@ hipError_t run_probe(const nr_index *ix, const float *logits, int64_t nq, int P,
     }
   }
   return nr::launch_probe(a, s);
+}
+
+// what a search of nq queries on these buffers finds at zero
+nr::ZeroArgs search_zero(const Buffers &B, int64_t nq) {
+  nr::ZeroArgs z{};
+  int i = 0;
+  auto add = [&](void *p, int words) {
+    z.p[i] = static_cast<int32_t *>(p);
+    z.n[i++] = words;
+  };
+  constexpr int counters = nr::TILE_COUNTERS * nr::TILE_COUNTER_STRIDE;
+  add(B.counter, counters);
+  add(B.tile_off + nq, 1);
+  if (B.shared) {
+    z.per_query[0] = B.scnt;
+    z.per_query[1] = B.flag;
+    add(B.counter2, counters);
+    add(B.wstats + 3, 2 * 4);  // counters 3 to 5, and the refinement's bytes
+    add(B.pool_cnt, 2);
+    add(B.open_cnt, 2);
+  } else {
+    add(B.wstats + 6, 2);
+  }
+  return z;
 }
 
 // after run_probe(..., &B) on the same buffers (it writes B.lk and B.redo)
@@ -519,7 +545,6 @@ hipError_t run_refine(const nr_index *ix, const void *q, int64_t nq, int k, cons
   pa.tile_off = B.tile_off;
   pa.tile_q = B.tile_q;
   pa.tile_c0 = B.tile_c0;
-  pa.counter = B.counter;
   pa.rfull = (o.qmask || o.own_cseed) ? nullptr : B.rfull;
   pa.qmask = o.qmask;
   pa.own_cseed = o.own_cseed;
@@ -536,8 +561,7 @@ hipError_t run_refine(const nr_index *ix, const void *q, int64_t nq, int k, cons
   }
   // the search's refine bytes count from its first refinement launch on (the
   // redo of queries whose survivors overflowed adds to them)
-  hipError_t e = o.qmask ? hipSuccess : nr::launch_fill_i32((int32_t *)(B.wstats + 6), 2, 0, s);
-  if (e == hipSuccess) e = nr::launch_plan(pa, s);
+  hipError_t e = nr::launch_plan(pa, s);
 #ifdef NR_PREP_ON_MAIN
   if (e == hipSuccess && o.prep) {
     e = nr::launch_shared_prep(*o.prep, s);
@@ -589,6 +613,7 @@ hipError_t run_refine(const nr_index *ix, const void *q, int64_t nq, int k, cons
   ma.k = k;
   ma.is_u8 = ix->d.dtype == NR_U8;
   ma.tile_off = B.tile_off;
+  ma.ntile = B.ntile;
   ma.pkey = B.pkey;
   ma.pid = B.pid;
   ma.rtot = B.rtot;
@@ -596,6 +621,10 @@ hipError_t run_refine(const nr_index *ix, const void *q, int64_t nq, int k, cons
   ma.out_dists = out_dists;
   ma.qstats = qstats;
   ma.qmask = o.qmask;
+  if (o.prep) {
+    ma.qrec = B.qrec;
+    ma.qnorm = B.qnorm;
+  }
   e = nr::launch_merge(ma, s);
   if (e == hipSuccess && ev) (void)hipEventRecord(ev[2], s);
   return e;
@@ -636,6 +665,7 @@ nr::SharedArgs shared_args(const nr_index *ix, const nr_params *p, const void *q
   a.rfull = B.rfull;
   a.rtot = B.rtot;
   a.tile_off = B.tile_off;
+  a.own_counter = B.counter;
   a.own_ids = B.own_ids;
   a.own_dists = B.own_dists;
   a.own_rows = B.own_rows;
@@ -1015,6 +1045,8 @@ nr_status nr_refine(const nr_index *cix, const void *queries, int64_t nq, int32_
   if (nr_status s = workspace_for(ix, stream, sh, &B, &w)) return s;
   for (int64_t q0 = 0; q0 < nq; q0 += sh.nq) {
     int64_t n = nq - q0 < sh.nq ? nq - q0 : sh.nq;
+    const nr::ZeroArgs z = search_zero(B, n);
+    for (int i = 0; i < 6; ++i) HIP_OK(nr::launch_fill_i32(z.p[i], z.n[i], 0, stream));
     HIP_OK(run_refine(ix, (const char *)queries + q0 * ix->d.d * elem_size(ix), n, k,
                       clusters + q0 * cap, n_clusters + q0, cap, B, out_ids + q0 * k,
                       out_dists + q0 * k, nullptr, stream, nullptr));
@@ -1057,7 +1089,8 @@ nr_status nr_search_ex(const nr_index *cix, const void *queries, const float *lo
     const float *lg = logits ? logits + q0 * ix->d.b : B.logits;
     if (!logits) HIP_OK(run_encode(ix, qp, n, B.logits, B, stream));
     if (prof) HIP_OK(hipEventRecord(es.ev[1], stream));
-    HIP_OK(run_probe(ix, lg, n, P, p, B.codes, B.costs, B.bins, B.counts, stream, &B));
+    const nr::ZeroArgs z = search_zero(B, n);
+    HIP_OK(run_probe(ix, lg, n, P, p, B.codes, B.costs, B.bins, B.counts, stream, &B, &z));
     if (prof) HIP_OK(hipEventRecord(es.ev[2], stream));
     nr::SharedArgs sa{};
     nr::PairHistArgs ph{};
@@ -1139,7 +1172,8 @@ nr_status nr_search_noalloc(const nr_index *cix, const void *queries, const floa
     const void *qp = (const char *)queries + q0 * qrow;
     const float *lg = logits ? logits + q0 * ix->d.b : B.logits;
     if (!logits) HIP_OK(run_encode(ix, qp, n, B.logits, B, stream));
-    HIP_OK(run_probe(ix, lg, n, P, p, B.codes, B.costs, B.bins, B.counts, stream, &B));
+    const nr::ZeroArgs z = search_zero(B, n);
+    HIP_OK(run_probe(ix, lg, n, P, p, B.codes, B.costs, B.bins, B.counts, stream, &B, &z));
     HIP_OK(run_route(ix, lg, n, P, p, B, B.clus, B.nclus, cap, nullptr, stream, nullptr, true));
     HIP_OK(run_refine(ix, qp, n, k, B.clus, B.nclus, cap, B, out_ids + q0 * k,
                       out_dists + q0 * k, nullptr, stream, nullptr));

@@ -121,7 +121,17 @@ struct EncodeLayerArgs {
   int N, K;
 };
 
+// words that a search sets to zero before its first use of them: the probe
+// kernel, which runs before every other kernel of the search but the encoder,
+// clears them on its way (seven fills took 5 us each)
+struct ZeroArgs {
+  int32_t *per_query[2];  // [nq] each, may be null
+  int32_t *p[6];
+  int n[6];               // words at p[i]
+};
+
 struct ProbeArgs {
+  ZeroArgs zero;
   const float *logits;   // [nq x b]
   const float *tau;      // [b]
   int64_t nq;
@@ -209,10 +219,9 @@ struct PlanArgs {
   uint32_t *rtot;        // [nq]
   uint32_t *tsize;       // [nq]
   int32_t *ntile;        // [nq]
-  int32_t *tile_off;     // [nq + 1]
+  int32_t *tile_off;     // [nq + 1] first tile of each query; [nq]: tiles (zero before)
   int32_t *tile_q;       // [nq x MAX_TILES_PER_QUERY]
   int32_t *tile_c0;
-  int32_t *counter;      // [TILE_COUNTERS x TILE_COUNTER_STRIDE] of the refinement kernel
   uint32_t *rfull;       // [nq] rows of the whole list, may be null
   const int32_t *qmask;  // [nq] only queries with qmask[q] != 0 get tiles, may be null
   const int32_t *own_cseed;  // [nq] may be null; else only list positions i < own_cseed[q] count
@@ -247,7 +256,7 @@ struct RefineArgs {
 struct MergeArgs {
   int64_t nq;
   int k, is_u8;
-  const int32_t *tile_off;
+  const int32_t *tile_off, *ntile;
   const uint32_t *pkey;
   const int64_t *pid;
   const uint32_t *rtot;
@@ -255,6 +264,8 @@ struct MergeArgs {
   float *out_dists;
   int32_t *qstats;
   const int32_t *qmask;  // only queries with qmask[q] != 0 are written, may be null
+  uint4 *qrec;           // [nq] the shared scan's record of each query, may be null
+  const uint2 *qnorm;    // [nq] uint8 rows, with qrec
 };
 
 // batch-shared refinement: a candidate row listed by several queries of the
@@ -278,7 +289,8 @@ struct SharedArgs {
   int32_t *cseed;             // [nq] leading clusters, scored by the query's own (seed) pass
   uint32_t *rfull;            // [nq] rows of the whole list
   const uint32_t *rtot;       // [nq] rows of the own pass
-  const int32_t *tile_off;    // [nq + 1] tiles of the own pass
+  int32_t *tile_off;          // [nq + 1] tiles of the own pass ([nq]: how many)
+  int32_t *own_counter;       // [TILE_COUNTERS x TILE_COUNTER_STRIDE] of the own pass
   const int64_t *own_ids;     // [nq x k] top-k of the own pass (sorted)
   const float *own_dists;
   uint32_t *own_rows;         // [nq] copy of rtot kept for diagnostics
