@@ -1,5 +1,5 @@
 // Step 1: encoder forward pass (Sec. 3.2.1; architecture Sec. 4.5, App. A),
-// one launch per linear layer.  Each layer is a dense contraction
+// one launch per linear layer, or one for the last two (k_encode_pair).  Each layer is a dense contraction
 //   out[m][n] = act( in_scale * sum_k in[m][k] * W[n][k] + bias[n] )
 // on the fp32 matrix cores (v_mfma_f32_16x16x4f32).  A 256-thread block owns a
 // BM x BN output tile and each of its four waves a (BM/2) x (BN/2) quarter, as
@@ -173,6 +173,204 @@ __global__ void __launch_bounds__(256) k_encode_layer(EncodeLayerArgs a) {
         a.out[m * N + n] = v;
       }
     }
+}
+
+// The last hidden layer and the code layer (at most 32 outputs) in one kernel:
+// a block owns BM rows, computes their hidden activations 64 at a time as above
+// (the next tile's first loads go out before its products), passes them through
+// LDS and adds each 64's products to the code layer's accumulators.  k runs in
+// increasing order in both chains, so the logits are those of the two kernels
+// bit for bit; the activations (1 KB a row at 256) never reach memory, and all
+// rows go in one launch.  Bound by the fp32 matrix cores.
+template <int BM, bool VEC>
+__global__ void __launch_bounds__(256) k_encode_pair(EncodeLayerArgs a, EncodeLayerArgs z) {
+  constexpr int BN = 64, BK = 16;
+  constexpr int MI = BM / 32, NJ = 2;
+  constexpr int VW = VEC ? 4 : 1;
+  constexpr int LA = BM * BK / VW, LW = BN * BK / VW;
+  constexpr int PA = (LA + 255) / 256, PW = (LW + 255) / 256;
+  __shared__ float As[2][BK][BM + 4];
+  __shared__ float Ws[2][BK][BN + 4];
+  __shared__ __attribute__((aligned(16))) float Hs[BN][BM + 4];  // activations, [k][row]
+  __shared__ float Zs[BN][32 + 4];                               // code layer, [k][output]
+  const int tid = threadIdx.x;
+  const int lane = tid & 63, wave = tid >> 6;
+  const int64_t m0 = (int64_t)blockIdx.x * BM;
+  const int wm = (wave & 1) * (BM / 2), wn = (wave >> 1) * (BN / 2);
+  const int K = a.K, N = a.N, NZ = z.N;
+  float ra[PA][VW], rw[PW][VW];
+  auto fetch = [&](int n0, int k0) {
+#pragma unroll
+    for (int u = 0; u < PA; ++u) {
+      const int e = tid + 256 * u;
+      const int r = e / (BK / VW), kk = VW * (e % (BK / VW));
+      if (LA % 256 != 0 && e >= LA) continue;
+      if constexpr (VEC) {
+        const float4 v = enc_load_in4(a, m0 + r, k0 + kk);
+        ra[u][0] = v.x;
+        ra[u][VW > 1 ? 1 : 0] = v.y;
+        ra[u][VW > 2 ? 2 : 0] = v.z;
+        ra[u][VW > 3 ? 3 : 0] = v.w;
+      } else {
+        ra[u][0] = enc_load_in(a, m0 + r, k0 + kk);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < PW; ++u) {
+      const int e = tid + 256 * u;
+      const int r = e / (BK / VW), kk = VW * (e % (BK / VW));
+      if (LW % 256 != 0 && e >= LW) continue;
+      if constexpr (VEC) {
+        const float4 v = enc_load_w4(a, n0 + r, k0 + kk);
+        rw[u][0] = v.x;
+        rw[u][VW > 1 ? 1 : 0] = v.y;
+        rw[u][VW > 2 ? 2 : 0] = v.z;
+        rw[u][VW > 3 ? 3 : 0] = v.w;
+      } else {
+        const int n = n0 + r, kg = k0 + kk;
+        rw[u][0] = (n < N && kg < K) ? a.W[(int64_t)n * K + kg] : 0.f;
+      }
+    }
+  };
+  auto stash = [&](int buf) {
+#pragma unroll
+    for (int u = 0; u < PA; ++u) {
+      const int e = tid + 256 * u;
+      const int r = e / (BK / VW), kk = VW * (e % (BK / VW));
+      if (LA % 256 != 0 && e >= LA) continue;
+#pragma unroll
+      for (int v = 0; v < VW; ++v) As[buf][kk + v][r] = ra[u][v];
+    }
+#pragma unroll
+    for (int u = 0; u < PW; ++u) {
+      const int e = tid + 256 * u;
+      const int r = e / (BK / VW), kk = VW * (e % (BK / VW));
+      if (LW % 256 != 0 && e >= LW) continue;
+#pragma unroll
+      for (int v = 0; v < VW; ++v) Ws[buf][kk + v][r] = rw[u][v];
+    }
+  };
+  // the wave's 16 x 16 blocks of the code layer: BM / 16 row blocks x 2
+  constexpr int NZB = BM / 32;
+  const int zr = BM == 64 ? wave : (wave & 1);
+  v4f zacc[NZB];
+#pragma unroll
+  for (int i = 0; i < NZB; ++i) zacc[i] = v4f{0.f, 0.f, 0.f, 0.f};
+  fetch(0, 0);
+  for (int n0 = 0; n0 < N; n0 += BN) {
+    // this tile's part of the code layer: thread -> k tid % 64, outputs tid / 64 + 4 i
+    float rz[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int k = n0 + (tid & 63), n = (tid >> 6) + 4 * i;
+      rz[i] = k < N && n < NZ ? z.W[(int64_t)n * N + k] : 0.f;
+    }
+    v4f acc[MI][NJ];
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) acc[i][j] = v4f{0.f, 0.f, 0.f, 0.f};
+    stash(0);
+    __syncthreads();
+    int buf = 0;
+    for (int k0 = 0; k0 < K; k0 += BK) {
+      const bool more = k0 + BK < K;
+      if (more) fetch(n0, k0 + BK);
+#pragma unroll
+      for (int kk = 0; kk < BK; kk += 4) {
+        const int kr = kk + (lane >> 4), c = lane & 15;
+        float av[MI], bv[NJ];
+#pragma unroll
+        for (int i = 0; i < MI; ++i) av[i] = As[buf][kr][wm + 16 * i + c];
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) bv[j] = Ws[buf][kr][wn + 16 * j + c];
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+          for (int j = 0; j < NJ; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[i], bv[j], acc[i][j], 0, 0, 0);
+      }
+      if (more) stash(buf ^ 1);
+      __syncthreads();
+      buf ^= 1;
+    }
+    if (n0 + BN < N) fetch(n0 + BN, 0);
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      const int col = wn + 16 * j + (lane & 15), n = n0 + col;
+      const bool ok = n < N;
+      const float bias = ok && a.bias ? a.bias[n] : 0.f;
+      const float sc = ok && a.bn_scale ? a.bn_scale[n] : 1.f;
+      const float sh = ok && a.bn_shift ? a.bn_shift[n] : 0.f;
+#pragma unroll
+      for (int i = 0; i < MI; ++i) {
+        float v[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          v[r] = acc[i][j][r] * a.in_scale + bias;
+          v[r] = v[r] * sc + sh;
+          v[r] = ok && v[r] > 0.f ? v[r] : 0.f;
+        }
+        *reinterpret_cast<float4 *>(&Hs[col][wm + 16 * i + 4 * (lane >> 4)]) =
+            make_float4(v[0], v[1], v[2], v[3]);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < 8; ++i) Zs[tid & 63][(tid >> 6) + 4 * i] = rz[i];
+    __syncthreads();
+#pragma unroll
+    for (int kk = 0; kk < BN; kk += 4) {
+      const int kr = kk + (lane >> 4), c = lane & 15;
+      const float av = Hs[kr][16 * zr + c];
+#pragma unroll
+      for (int i = 0; i < NZB; ++i) {
+        const int zc = BM == 64 ? i : (wave >> 1);
+        zacc[i] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, Zs[kr][16 * zc + c], zacc[i], 0, 0, 0);
+      }
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < NZB; ++i) {
+    const int zc = BM == 64 ? i : (wave >> 1);
+    const int n = 16 * zc + (lane & 15);
+    if (n >= NZ) continue;
+    const float bias = z.bias ? z.bias[n] : 0.f;
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int64_t m = m0 + 16 * zr + 4 * (lane >> 4) + r;
+      if (m < a.M) z.out[m * NZ + n] = zacc[i][r] * z.in_scale + bias;
+    }
+  }
+}
+
+// A pair goes to one kernel where the rows fill the chip by themselves: a block
+// walks all of the hidden layer, so few rows end with few blocks' chains, and a
+// block per tile of each layer is faster (128 -> 256 -> 16 inside a search: one
+// row 18 us in two kernels, 28 in one; 10,000 rows 24 and 27).  From 16,384
+// rows on there are two blocks per CU; wide layers (longer chains) need more.
+// 1M rows of 128 -> 256 -> 24: 1.96 ms in two kernels per 16,384 rows, 0.99 in
+// one (82 TFLOP/s of fp32)
+bool encode_pair(int64_t M, int K, int N, int NZ) {
+  return NZ <= 32 && M >= ((int64_t)K * N <= 65536 ? 16384 : 65536);
+}
+
+hipError_t launch_encode_pair(const EncodeLayerArgs &a, const EncodeLayerArgs &z, hipStream_t s) {
+  if (a.M <= 0) return hipSuccess;
+  if (z.N > 32 || z.K != a.N || !a.relu || z.relu) return hipErrorInvalidValue;
+  const bool vec = a.K % 4 == 0 && (reinterpret_cast<uintptr_t>(a.in) & 15) == 0 &&
+                   (reinterpret_cast<uintptr_t>(a.W) & 15) == 0;
+  // 64 rows a block where that still gives each CU three (the LDS's share)
+  const bool big = a.M >= 64 * 768;
+  const dim3 grid((unsigned)(big ? (a.M + 63) / 64 : (a.M + 31) / 32));
+  if (big && vec)
+    hipLaunchKernelGGL((k_encode_pair<64, true>), grid, dim3(256), 0, s, a, z);
+  else if (big)
+    hipLaunchKernelGGL((k_encode_pair<64, false>), grid, dim3(256), 0, s, a, z);
+  else if (vec)
+    hipLaunchKernelGGL((k_encode_pair<32, true>), grid, dim3(256), 0, s, a, z);
+  else
+    hipLaunchKernelGGL((k_encode_pair<32, false>), grid, dim3(256), 0, s, a, z);
+  return hipGetLastError();
 }
 
 template <int BM, int BN, int BK>

@@ -387,6 +387,7 @@ hipError_t run_encode(const nr_index *ix, const void *q, int64_t nq, float *logi
   const void *in = q;
   int in_u8 = ix->d.dtype == NR_U8;
   float *bufs[2] = {B.act0, B.act1};
+  nr::EncodeLayerArgs prev{};
   for (int l = 0; l < L; ++l) {
     nr::EncodeLayerArgs a{};
     a.in = in;
@@ -401,7 +402,11 @@ hipError_t run_encode(const nr_index *ix, const void *q, int64_t nq, float *logi
     a.M = nq;
     a.K = ix->widths[l];
     a.N = ix->widths[l + 1];
-    hipError_t e = nr::launch_encode_layer(a, s);
+    if (l + 2 == L && nr::encode_pair(nq, a.K, a.N, ix->widths[L])) {
+      prev = a;  // goes with the code layer
+      continue;
+    }
+    hipError_t e = prev.W ? nr::launch_encode_pair(prev, a, s) : nr::launch_encode_layer(a, s);
     if (e != hipSuccess) return e;
     in = a.out;
     in_u8 = 0;
@@ -978,6 +983,12 @@ nr_status nr_encode(const nr_index *cix, const void *queries, int64_t nq, float 
   if (nq < 0) return fail(NR_EINVAL, "nq must be >= 0");
   if (nq == 0) return NR_OK;
   if (!queries || !logits) return fail(NR_EINVAL, "queries and logits must not be NULL");
+  const int L = (int)ix->widths.size() - 1;
+  if (L == 1 || (L == 2 && nr::encode_pair(nq, ix->widths[0], ix->widths[1], ix->widths[2]))) {
+    // one kernel, no activations to hold: all rows at once
+    HIP_OK(run_encode(ix, queries, nq, logits, Buffers{}, stream));
+    return NR_OK;
+  }
   Buffers B;
   Workspace *w;
   Shape sh = shape_of(ix, nq, 1, 1, 1);

@@ -1,0 +1,49 @@
+"""The last two encoder layers in one kernel: its logits are those of two
+kernels bit for bit (a 2-layer encoder against the same layers behind an
+identity layer of whole numbers, which keeps every value but takes the inputs
+through another kernel), at row counts around the blocks and at widths that are
+no multiple of a tile; and against fp64."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2608_15438_amd import index_build as IB
+from paper_2608_15438_amd import neuroute as NR
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("u8", [True, False])
+@pytest.mark.parametrize("d,h,b", [(128, 256, 24), (96, 200, 15), (48, 64, 30), (36, 1, 1),
+                                   (20, 65, 16), (1536, 33, 9)])
+@pytest.mark.parametrize("m", [33, 16_383, 16_385, 49_151, 49_153])
+def test_pair_logits(u8, d, h, b, m):
+    if u8 and d % 16:
+        d = d + 16 - d % 16
+    rng = np.random.default_rng(d * m)
+    W = [rng.standard_normal((h, d)).astype(np.float32) / np.float32(np.sqrt(d)),
+         rng.standard_normal((b, h)).astype(np.float32) / np.float32(np.sqrt(h))]
+    bias = [rng.standard_normal(h).astype(np.float32), rng.standard_normal(b).astype(np.float32)]
+    g = torch.Generator(device="cuda").manual_seed(m)
+    if u8:
+        x = torch.randint(0, 256, (m, d), generator=g, device="cuda", dtype=torch.uint8)
+    else:
+        x = torch.rand((m, d), generator=g, device="cuda")
+    dt = NR.NR_U8 if u8 else NR.NR_F32
+    ix = NR.Index.encoder_only(IB.Encoder(W, bias, 1.0), dt)
+    got = ix.nr_encode(x)
+    xd = x.double()
+    hid = xd @ torch.from_numpy(W[0]).cuda().double().T + torch.from_numpy(bias[0]).cuda().double()
+    w1 = torch.from_numpy(W[1]).cuda().double()
+    want = hid.clamp_min(0) @ w1.T + torch.from_numpy(bias[1]).cuda().double()
+    mag = (xd.abs() @ torch.from_numpy(np.abs(W[0])).cuda().double().T + 3) @ w1.abs().T + 3
+    # two chains of d and h products: at most d + h + 4 roundings of the magnitudes
+    assert ((got - want).abs() <= (d + h + 4) * 2.0 ** -24 * mag).all()
+    if d <= 128:
+        eye = IB.Encoder([np.eye(d, dtype=np.float32)] + W, [np.zeros(d, np.float32)] + bias, 1.0)
+        ix3 = NR.Index.encoder_only(eye, dt)
+        assert torch.equal(got, ix3.nr_encode(x))
+        ix3.close()
+    # rows do not depend on the batch they come in
+    assert torch.equal(got[m // 2:m // 2 + 1], ix.nr_encode(x[m // 2:m // 2 + 1].clone()))
+    ix.close()
