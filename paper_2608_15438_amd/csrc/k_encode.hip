@@ -42,16 +42,46 @@ __device__ __forceinline__ float4 enc_load_w4(const EncodeLayerArgs &a, int n, i
   return *reinterpret_cast<const float4 *>(a.W + (int64_t)n * a.K + kg);
 }
 
+// K-tiles of 16 are kept by row in LDS, KS floats apart, k = 4 s + g at slot
+// 4 g + s: lane l of a 16x16x4 block takes k = l / 16 of each of four steps, so
+// its operands for all four are one 16-byte read, and reads and writes fall on
+// different banks (by k, with a read per operand and up to three lanes on a
+// bank: 1M rows of 128 -> 256 -> 24 988 us, so 966; 10,000 of 1536 -> 512 the same).
+// Tiles of 128 x 64, 64 x 128 and 128 x 128 are no faster (5, 4 and 24 % slower
+// for the 1536-d encoder)
+constexpr int KS = 20;
+__device__ __forceinline__ constexpr int enc_slot(int k) { return 4 * (k & 3) + (k >> 2); }
+
+template <int MI, int NJ>
+__device__ __forceinline__ void enc_ktile(v4f (&acc)[MI][NJ], const float *A, const float *W) {
+  const int at = (lane_id() & 15) * KS + 4 * (lane_id() >> 4);
+  float4 a4[MI], b4[NJ];
+#pragma unroll
+  for (int i = 0; i < MI; ++i) a4[i] = *reinterpret_cast<const float4 *>(A + 16 * i * KS + at);
+#pragma unroll
+  for (int j = 0; j < NJ; ++j) b4[j] = *reinterpret_cast<const float4 *>(W + 16 * j * KS + at);
+#pragma unroll
+  for (int s = 0; s < 4; ++s)
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int j = 0; j < NJ; ++j) {
+        const float av = s == 0 ? a4[i].x : s == 1 ? a4[i].y : s == 2 ? a4[i].z : a4[i].w;
+        const float bv = s == 0 ? b4[j].x : s == 1 ? b4[j].y : s == 2 ? b4[j].z : b4[j].w;
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(av, bv, acc[i][j], 0, 0, 0);
+      }
+}
+
 template <int BM, int BN, int BK, bool VEC>
 __global__ void __launch_bounds__(256) k_encode_layer(EncodeLayerArgs a) {
   constexpr int MI = BM / 32, NJ = BN / 32;  // 16 x 16 blocks per wave
   constexpr int VW = VEC ? 4 : 1;            // elements per load
   constexpr int LA = BM * BK / VW, LW = BN * BK / VW;  // loads per tile
   constexpr int PA = (LA + 255) / 256, PW = (LW + 255) / 256;  // per thread (at most)
-  static_assert(BK % 4 == 0 && BM % 32 == 0 && BN % 32 == 0, "whole MFMA blocks");
-  // two K-tiles of A (activations) and W, each [BK][B* + 4]
-  __shared__ float As[2][BK][BM + 4];
-  __shared__ float Ws[2][BK][BN + 4];
+  static_assert(BK == 16 && BM % 32 == 0 && BN % 32 == 0, "whole MFMA blocks");
+  // two K-tiles of A (activations) and W
+  __shared__ __attribute__((aligned(16))) float As[2][BM][KS];
+  __shared__ __attribute__((aligned(16))) float Ws[2][BN][KS];
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
   // tile of this block: the column tiles of one row tile are consecutive
@@ -113,7 +143,7 @@ __global__ void __launch_bounds__(256) k_encode_layer(EncodeLayerArgs a) {
       const int r = e / (BK / VW), kk = VW * (e % (BK / VW));
       if (LA % 256 != 0 && e >= LA) continue;
 #pragma unroll
-      for (int v = 0; v < VW; ++v) As[buf][kk + v][r] = ra[u][v];
+      for (int v = 0; v < VW; ++v) As[buf][r][enc_slot(kk + v)] = ra[u][v];
     }
 #pragma unroll
     for (int u = 0; u < PW; ++u) {
@@ -121,7 +151,7 @@ __global__ void __launch_bounds__(256) k_encode_layer(EncodeLayerArgs a) {
       const int r = e / (BK / VW), kk = VW * (e % (BK / VW));
       if (LW % 256 != 0 && e >= LW) continue;
 #pragma unroll
-      for (int v = 0; v < VW; ++v) Ws[buf][kk + v][r] = rw[u][v];
+      for (int v = 0; v < VW; ++v) Ws[buf][r][enc_slot(kk + v)] = rw[u][v];
     }
   };
   fetch(0);
@@ -131,21 +161,7 @@ __global__ void __launch_bounds__(256) k_encode_layer(EncodeLayerArgs a) {
   for (int k0 = 0; k0 < K; k0 += BK) {
     const bool more = k0 + BK < K;
     if (more) fetch(k0 + BK);
-#pragma unroll
-    for (int kk = 0; kk < BK; kk += 4) {
-      // A operand of a 16x16x4 block: lane l holds row l % 16, k l / 16
-      const int kr = kk + (lane >> 4), c = lane & 15;
-      float av[MI], bv[NJ];
-#pragma unroll
-      for (int i = 0; i < MI; ++i) av[i] = As[buf][kr][wm + 16 * i + c];
-#pragma unroll
-      for (int j = 0; j < NJ; ++j) bv[j] = Ws[buf][kr][wn + 16 * j + c];
-#pragma unroll
-      for (int i = 0; i < MI; ++i)
-#pragma unroll
-        for (int j = 0; j < NJ; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[i], bv[j], acc[i][j], 0, 0, 0);
-    }
+    enc_ktile<MI, NJ>(acc, &As[buf][wm][0], &Ws[buf][wn][0]);
     if (more) stash(buf ^ 1);
     __syncthreads();
     buf ^= 1;
@@ -189,8 +205,8 @@ __global__ void __launch_bounds__(256) k_encode_pair(EncodeLayerArgs a, EncodeLa
   constexpr int VW = VEC ? 4 : 1;
   constexpr int LA = BM * BK / VW, LW = BN * BK / VW;
   constexpr int PA = (LA + 255) / 256, PW = (LW + 255) / 256;
-  __shared__ float As[2][BK][BM + 4];
-  __shared__ float Ws[2][BK][BN + 4];
+  __shared__ __attribute__((aligned(16))) float As[2][BM][KS];
+  __shared__ __attribute__((aligned(16))) float Ws[2][BN][KS];
   __shared__ __attribute__((aligned(16))) float Hs[BN][BM + 4];  // activations, [k][row]
   __shared__ float Zs[BN][32 + 4];                               // code layer, [k][output]
   const int tid = threadIdx.x;
@@ -239,7 +255,7 @@ __global__ void __launch_bounds__(256) k_encode_pair(EncodeLayerArgs a, EncodeLa
       const int r = e / (BK / VW), kk = VW * (e % (BK / VW));
       if (LA % 256 != 0 && e >= LA) continue;
 #pragma unroll
-      for (int v = 0; v < VW; ++v) As[buf][kk + v][r] = ra[u][v];
+      for (int v = 0; v < VW; ++v) As[buf][r][enc_slot(kk + v)] = ra[u][v];
     }
 #pragma unroll
     for (int u = 0; u < PW; ++u) {
@@ -247,7 +263,7 @@ __global__ void __launch_bounds__(256) k_encode_pair(EncodeLayerArgs a, EncodeLa
       const int r = e / (BK / VW), kk = VW * (e % (BK / VW));
       if (LW % 256 != 0 && e >= LW) continue;
 #pragma unroll
-      for (int v = 0; v < VW; ++v) Ws[buf][kk + v][r] = rw[u][v];
+      for (int v = 0; v < VW; ++v) Ws[buf][r][enc_slot(kk + v)] = rw[u][v];
     }
   };
   // the wave's 16 x 16 blocks of the code layer: BM / 16 row blocks x 2
@@ -276,20 +292,7 @@ __global__ void __launch_bounds__(256) k_encode_pair(EncodeLayerArgs a, EncodeLa
     for (int k0 = 0; k0 < K; k0 += BK) {
       const bool more = k0 + BK < K;
       if (more) fetch(n0, k0 + BK);
-#pragma unroll
-      for (int kk = 0; kk < BK; kk += 4) {
-        const int kr = kk + (lane >> 4), c = lane & 15;
-        float av[MI], bv[NJ];
-#pragma unroll
-        for (int i = 0; i < MI; ++i) av[i] = As[buf][kr][wm + 16 * i + c];
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) bv[j] = Ws[buf][kr][wn + 16 * j + c];
-#pragma unroll
-        for (int i = 0; i < MI; ++i)
-#pragma unroll
-          for (int j = 0; j < NJ; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[i], bv[j], acc[i][j], 0, 0, 0);
-      }
+      enc_ktile<MI, NJ>(acc, &As[buf][wm][0], &Ws[buf][wn][0]);
       if (more) stash(buf ^ 1);
       __syncthreads();
       buf ^= 1;
@@ -348,8 +351,8 @@ __global__ void __launch_bounds__(256) k_encode_pair(EncodeLayerArgs a, EncodeLa
 // block per tile of each layer is faster (128 -> 256 -> 16 inside a search: one
 // row 18 us in two kernels, 28 in one; 10,000 rows 24 and 27).  From 16,384
 // rows on there are two blocks per CU; wide layers (longer chains) need more.
-// 1M rows of 128 -> 256 -> 24: 1.96 ms in two kernels per 16,384 rows, 0.99 in
-// one (82 TFLOP/s of fp32)
+// 1M rows of 128 -> 256 -> 24: 1.96 ms in two kernels per 16,384 rows, 0.97 in
+// one (84 TFLOP/s of fp32)
 bool encode_pair(int64_t M, int K, int N, int NZ) {
   return NZ <= 32 && M >= ((int64_t)K * N <= 65536 ? 16384 : 65536);
 }
