@@ -4,8 +4,8 @@
 //  plan   (one wave per query)  row prefix over the query's clusters, total
 //         rows R_q, tile size T_q = max(smallest, ceil(R_q / 64)) and the
 //         (query, row range) tiles;
-//  refine (persistent waves)    each wave takes tiles from an atomic counter
-//         and walks the tile's virtual rows; 8 lanes cover one 128-byte row
+//  refine (persistent waves)    each wave takes tiles (its own number's, or
+//         from one of a few atomic counters) and walks the tile's virtual rows; 8 lanes cover one 128-byte row
 //         segment with one 16-byte load each, so a wave instruction reads 8
 //         full cache lines; U rows per lane group are in flight;
 //         uint8:  |x - q|^2 = x.x - 2 x.q + q.q with packed u8 dot products,

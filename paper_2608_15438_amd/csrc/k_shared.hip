@@ -17,8 +17,8 @@
 //          counts) form the scan list in cluster order with their pair and
 //          work ranges (rows x groups of <= g queries); the pairs are then
 //          scattered by cluster;
-//  scan    persistent waves take tiles of the work space from an atomic
-//          counter and gather consecutive units of the tile into batches
+//  scan    persistent waves take tiles of the work space (their own number's,
+//          or from a few atomic counters) and gather consecutive units of the tile into batches
 //          whose query rows sit in LDS.  Each row's head (its first
 //          scan_head bytes) is read once for all queries of its unit and
 //          drops the pairs whose head part alone exceeds the bound; the
