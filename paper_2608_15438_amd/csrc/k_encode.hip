@@ -348,8 +348,8 @@ __global__ void __launch_bounds__(256) k_encode_pair(EncodeLayerArgs a, EncodeLa
 
 // A pair goes to one kernel where the rows fill the chip by themselves: a block
 // walks all of the hidden layer, so few rows end with few blocks' chains, and a
-// block per tile of each layer is faster (128 -> 256 -> 16 inside a search: one
-// row 18 us in two kernels, 28 in one; 10,000 rows 24 and 27).  From 16,384
+// block per tile of each layer is faster (whole searches behind 128 -> 256 -> 16:
+// one query 64 us with two kernels, 74 with one; 10,000 558 and 561).  From 16,384
 // rows on there are two blocks per CU; wide layers (longer chains) need more.
 // 1M rows of 128 -> 256 -> 24: 1.96 ms in two kernels per 16,384 rows, 0.97 in
 // one (84 TFLOP/s of fp32)

@@ -52,7 +52,7 @@ __device__ __forceinline__ int clamp_count(int32_t n, int64_t cap) {
 // One wave per query: the rows before each of its clusters, its tile size, its
 // tiles (numbered from one atomic per block, so in any order: the merge orders
 // the results) and each tile's first cluster.  (As three kernels -- rows, a
-// scan over the queries, tiles -- 14 us for one query, 35 for 10,000.)
+// scan over the queries, tiles -- 12 us for one query, 35 for 10,000.)
 constexpr int PLAN_WAVES = 16;
 __global__ void __launch_bounds__(PLAN_WAVES * WAVE) k_plan(PlanArgs a) {
   __shared__ int32_t s_nt[PLAN_WAVES];
@@ -213,9 +213,8 @@ __device__ __forceinline__ void ltopk_insert(LazyTopK &t, int k, uint32_t ck, ui
 // Candidates of one step (one per lane of `m`, payload row cp), all at once:
 // their ids and the list's unread ones are loaded, the candidates sorted by
 // (key, id) -- ids are below 2^32 -- and merged with the list.  While a list
-// fills, a step of 64 rows holds tens of entrants: one such merge takes about
-// as long as three insertions.
-constexpr int BATCH_MIN = 5;   // entrants of a step from which they go together
+// fills, a step of 64 rows holds tens of entrants, each an insertion otherwise.
+constexpr int BATCH_MIN = 5;   // entrants of a step from which they go together (3 to 12 alike)
 __device__ __forceinline__ void ltopk_batch(LazyTopK &t, int k, uint64_t m, uint32_t ck,
                                             uint32_t cp, const int64_t *row_ids) {
   const int lane = lane_id();
