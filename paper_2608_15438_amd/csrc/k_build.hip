@@ -841,7 +841,6 @@ struct FinArgs {
   int b;
   const uint64_t *boff;
   const uint32_t *ids, *kb, *label, *ccnt;
-  const uint64_t *kbpre;
   const double *cent;
   int bp;
   const uint4 *slot;
@@ -1096,7 +1095,6 @@ hipError_t run_build_index(const BuildArgs &A, hipStream_t s) {
   f.kb = A.kb;
   f.label = A.label;
   f.ccnt = A.ccnt;
-  f.kbpre = A.kbpre;
   f.cent = A.cent;
   f.bp = build_pad(A.b);
   f.slot = A.slot;
