@@ -12,9 +12,9 @@
 // are centred on the batch mean first (distances do not change), which keeps
 // the norms, and so the cancellation in the expansion, small; k_center writes
 // them in rows of whole 64-byte groups, so the tiles load 16 bytes at a time
-// without bounds checks.  Norms and the expansion are taken in fp64: what
-// rounds is the fp32 chain of the dot products, two chains of every other
-// K-tile.
+// without bounds checks.  Sums, norms and dot products are fp32 chains in a
+// fixed order (rows of a block, blocks, dimensions), because pairs at the
+// mask's thresholds come in or drop out on one ulp and trained weights follow.
 //
 // k_pair_quantile: an order statistic of the off-diagonal distances (tau_emb
 // of a batch) by radix select over their bits.
@@ -30,6 +30,8 @@
 // the gradient is the same bit for bit on every run.  Only the numerator's
 // block sums meet in a double-precision atomic (its last bits may vary; the
 // mask count is exact).
+#include <algorithm>
+
 #include "nr_internal.h"
 
 namespace nr {
@@ -39,18 +41,25 @@ typedef float v4f_l __attribute__((ext_vector_type(4)));
 constexpr int LS_M = 64, LS_K = 16;
 
 // Column sums of x over blocks of LS_ROWS rows (partial[blk][c]), then the
-// column means (the partials added in block order).  4096 x 128 rows: 62 us
-// with 256 rows per block (16 blocks, one long chain each), 4 us with 32.
-constexpr int LS_ROWS = 32;
+// column means (the partials added in block order).  A column's sum is one
+// chain over the block's rows, so its loads go out 64 at a time (4096 x 128 rows:
+// 62 us one after the other, 12 us so).
+constexpr int LS_ROWS = 256;
 
-__global__ void __launch_bounds__(128) k_col_partial(const float *x, int64_t B, int D,
-                                                     float *partial) {
+__global__ void __launch_bounds__(64) k_col_partial(const float *x, int64_t B, int D,
+                                                    float *partial) {
   const int64_t r0 = (int64_t)blockIdx.x * LS_ROWS;
   const int nr = (int)(B - r0 < LS_ROWS ? B - r0 : LS_ROWS);
-  for (int c = threadIdx.x; c < D; c += 128) {
+  for (int64_t c = blockIdx.y * 64 + threadIdx.x; c < D; c += gridDim.y * 64) {
+    const float *col = x + r0 * D + c;
     float s = 0.0f;
-#pragma unroll 8
-    for (int i = 0; i < nr; ++i) s += x[(r0 + i) * D + c];
+    for (int i0 = 0; i0 < nr; i0 += 64) {
+      float v[64];
+#pragma unroll
+      for (int u = 0; u < 64; ++u) v[u] = i0 + u < nr ? col[(int64_t)(i0 + u) * D] : 0.0f;
+#pragma unroll
+      for (int u = 0; u < 64; ++u) s += v[u];
+    }
     partial[(int64_t)blockIdx.x * D + c] = s;
   }
 }
@@ -62,35 +71,36 @@ __global__ void __launch_bounds__(64) k_col_mean(const float *partial, int64_t n
   double s = 0.0;
 #pragma unroll 16
   for (int64_t b = 0; b < nblk; ++b) s += partial[b * D + c];
-  // any shift leaves the distances as they are: one of 12 bits keeps most of
-  // the differences x - mean exact
-  mean[c] = __uint_as_float(__float_as_uint((float)(s / (double)B)) & 0xfffff000u);
+  mean[c] = (float)(s / (double)B);
 }
 
-// centred rows xc [B][DP], zeros from D on, and their squared norms; one wave
-// per row
+// centred rows xc [B][DP], zeros from D on, and their squared norms (one chain
+// over the dimensions in order); one wave per row
 __global__ void __launch_bounds__(256) k_center(const float *x, int64_t B, int D, int DP,
-                                                const float *mean, float *xc, double *norm) {
+                                                const float *mean, float *xc, float *norm) {
   const int lane = lane_id();
   const int64_t i = (int64_t)blockIdx.x * 4 + threadIdx.x / WAVE;
   if (i >= B) return;
-  double s = 0.0;
-  for (int c = lane; c < DP; c += WAVE) {
+  float s = 0.0f;
+  for (int c0 = 0; c0 < DP; c0 += WAVE) {
+    const int c = c0 + lane;
     const float v = c < D ? x[i * D + c] - mean[c] : 0.0f;
-    xc[i * DP + c] = v;
-    s += (double)v * (double)v;
+    if (c < DP) xc[i * DP + c] = v;
+#pragma unroll
+    for (int u = 0; u < WAVE; ++u) {   // zeros from D on leave the sum as it is
+      const float t = bcast_f32(v, u);
+      s = fmaf(t, t, s);
+    }
   }
-  for (int m = 1; m < WAVE; m <<= 1) s += __shfl_xor(s, m);
   if (lane == 0) norm[i] = s;
 }
 
 // Tiles on and above the diagonal only; each writes its mirror too, so the
 // matrix is symmetric bit for bit.  The next K-tile is loaded while this one
 // is multiplied (two LDS buffers).  4096 rows of 128: 69 us with element-wise
-// loads and stores of the mirror, 42 us with 16-byte ones and fp64 norms (which
-// bring the distances' error against 64 bits from 4.7e-7 to 1.8e-7).
+// loads and stores of the mirror, 39 us with 16-byte ones.
 __global__ void __launch_bounds__(256) k_pair_sqdist(const float *xc, int64_t B, int DP,
-                                                      const double *norm, float *out, int vec) {
+                                                      const float *norm, float *out, int vec) {
   __shared__ float As[2][LS_K][LS_M + 4];
   __shared__ float Bs[2][LS_K][LS_M + 4];
   const int tid = threadIdx.x;
@@ -103,10 +113,9 @@ __global__ void __launch_bounds__(256) k_pair_sqdist(const float *xc, int64_t B,
   const uint32_t bi = t - (uint32_t)((uint64_t)bj * (bj + 1) / 2);
   const int64_t i0 = (int64_t)bi * LS_M, j0 = (int64_t)bj * LS_M;
   const int wm = (wave & 1) * 32, wn = (wave >> 1) * 32;
-  v4f_l acc[2][2][2];   // [K-tile parity]
-  for (int p = 0; p < 2; ++p)
-    for (int i = 0; i < 2; ++i)
-      for (int j = 0; j < 2; ++j) acc[p][i][j] = v4f_l{0.f, 0.f, 0.f, 0.f};
+  v4f_l acc[2][2];
+  for (int i = 0; i < 2; ++i)
+    for (int j = 0; j < 2; ++j) acc[i][j] = v4f_l{0.f, 0.f, 0.f, 0.f};
   // thread -> row tid / 4, four columns from 4 (tid % 4) (rows past B repeat
   // the last one and are not written)
   const int lr = tid >> 2, lk = (tid & 3) * 4;
@@ -143,8 +152,7 @@ __global__ void __launch_bounds__(256) k_pair_sqdist(const float *xc, int64_t B,
       for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j)
-          acc[buf][i][j] =
-              __builtin_amdgcn_mfma_f32_16x16x4f32(av[i], bv[j], acc[buf][i][j], 0, 0, 0);
+          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[i], bv[j], acc[i][j], 0, 0, 0);
     }
     if (more) stash(buf ^ 1);
     __syncthreads();
@@ -161,13 +169,12 @@ __global__ void __launch_bounds__(256) k_pair_sqdist(const float *xc, int64_t B,
       const int64_t cj = j0 + wn + 16 * j + (lane & 15);
       const int64_t r0 = i0 + wm + 16 * i + 4 * (lane >> 4);
       if (cj >= B) continue;
-      const double nj = norm[cj];
+      const float nj = norm[cj];
       float v[4];
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int64_t ri = r0 + r;
-        const double ni = norm[ri < B ? ri : B - 1];
-        v[r] = (float)((ni + nj) - 2.0 * ((double)acc[0][i][j][r] + (double)acc[1][i][j][r]));
+        v[r] = (norm[ri < B ? ri : B - 1] + nj) - 2.0f * acc[i][j][r];
         v[r] = v[r] > 0.f ? v[r] : 0.f;
         if (ri == cj) v[r] = 0.f;
         if (ri < B) out[ri * B + cj] = v[r];
@@ -479,7 +486,7 @@ __global__ void __launch_bounds__(64 * LG_WAVES) k_lsim_grad(const float *d2, co
       }
     }
   }
-  // the gradient: a wave's four subsets, then the waves, in a fixed order
+  // the gradient: a wave's four subsets, then the waves, in pairs
   __syncthreads();
   float *gs = li_s;   // [wave][column][L]
 #pragma unroll
@@ -499,10 +506,15 @@ __global__ void __launch_bounds__(64 * LG_WAVES) k_lsim_grad(const float *d2, co
   }
   __syncthreads();
   for (int e = tid; e < LG_COLS * L; e += 64 * LG_WAVES) {
-    float v = 0.f;
-    for (int k = 0; k < LG_WAVES; ++k) v += gs[k * LG_COLS * L + e];
+    float v[LG_WAVES];
+#pragma unroll
+    for (int k = 0; k < LG_WAVES; ++k) v[k] = gs[k * LG_COLS * L + e];
+#pragma unroll
+    for (int d = 1; d < LG_WAVES; d <<= 1)
+#pragma unroll
+      for (int k = 0; k < LG_WAVES; k += 2 * d) v[k] += v[k + d];
     const int64_t jj = (int64_t)blockIdx.x * LG_COLS + e / L;
-    if (jj < B) grad[jj * L + e % L] = v;
+    if (jj < B) grad[jj * L + e % L] = v[0];
   }
   if (tid == 0) {
     double tn = 0.0, tc = 0.0;
@@ -520,7 +532,7 @@ static int center_stride(int D) { return (D + LS_K - 1) / LS_K * LS_K; }
 size_t pair_sqdist_ws_floats(int64_t B, int D) {
   // the centred rows from a 16-byte boundary on, then partial sums, means, norms
   return 4 + (size_t)B * center_stride(D) +
-         (size_t)((B + LS_ROWS - 1) / LS_ROWS + 1) * (size_t)D + 2 * (size_t)B;
+         (size_t)((B + LS_ROWS - 1) / LS_ROWS + 1) * (size_t)D + (size_t)B;
 }
 
 hipError_t launch_pair_sqdist(const float *x, int64_t B, int D, float *ws, float *out,
@@ -529,9 +541,9 @@ hipError_t launch_pair_sqdist(const float *x, int64_t B, int D, float *ws, float
   const int64_t nblk = (B + LS_ROWS - 1) / LS_ROWS;
   const int DP = center_stride(D);
   float *xc = reinterpret_cast<float *>((reinterpret_cast<uintptr_t>(ws) + 15) & ~(uintptr_t)15);
-  double *norm = reinterpret_cast<double *>(xc + B * DP);   // DP: whole 64-byte groups
-  float *partial = reinterpret_cast<float *>(norm + B), *mean = partial + nblk * D;
-  hipLaunchKernelGGL(k_col_partial, dim3((unsigned)nblk), dim3(128), 0, s, x, B, D, partial);
+  float *norm = xc + B * DP, *partial = norm + B, *mean = partial + nblk * D;
+  hipLaunchKernelGGL(k_col_partial, dim3((unsigned)nblk, (unsigned)std::min((D + 63) / 64, 65535)),
+                     dim3(64), 0, s, x, B, D, partial);
   hipLaunchKernelGGL(k_col_mean, dim3((unsigned)((D + 63) / 64)), dim3(64), 0, s, partial, nblk, B,
                      D, mean);
   hipLaunchKernelGGL(k_center, dim3((unsigned)((B + 3) / 4)), dim3(256), 0, s, x, B, D, DP, mean,

@@ -47,6 +47,23 @@ def test_pair_sqdist_edges(B, D):
     assert torch.equal(d2, d2.T)
 
 
+@pytest.mark.parametrize("offset", [0.0, 1e3, 1e4, 1e5, -3e5])
+@pytest.mark.parametrize("B,D", [(256, 128), (300, 20), (65, 200)])
+def test_pair_sqdist_offset(B, D, offset):
+    # columns far from zero: the centring takes the offset out, so the error
+    # stays that of the spread (the exact distances of the fp32 rows)
+    g = torch.Generator(device="cuda").manual_seed(B)
+    sign = torch.where(torch.arange(D, device="cuda") % 3 > 0, 1.0, -1.37)
+    x = torch.randn((B, D), generator=g, device="cuda") + offset * sign
+    d2 = NR.nr_pair_sqdist(x)
+    xd = x.double()
+    want = ((xd[:, None] - xd[None]) ** 2).sum(-1)
+    scale = float(((xd - xd.mean(0)) ** 2).sum(1).max())
+    # as above: at most D + 4 roundings of the scale for each norm and product
+    assert float((d2 - want).abs().max()) <= 4 * (D + 4) * 2.0 ** -24 * scale
+    assert torch.equal(d2, d2.T)
+
+
 @pytest.mark.parametrize("B,L", [(17, 1), (300, 3), (1030, 4), (515, 17), (256, 31), (700, 32)])
 def test_lsim_grad_widths(B, L):
     g = torch.Generator(device="cuda").manual_seed(L)
