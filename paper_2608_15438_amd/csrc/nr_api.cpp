@@ -985,8 +985,15 @@ nr_status nr_encode(const nr_index *cix, const void *queries, int64_t nq, float 
   if (!queries || !logits) return fail(NR_EINVAL, "queries and logits must not be NULL");
   const int L = (int)ix->widths.size() - 1;
   if (L == 1 || (L == 2 && nr::encode_pair(nq, ix->widths[0], ix->widths[1], ix->widths[2]))) {
-    // one kernel, no activations to hold: all rows at once
-    HIP_OK(run_encode(ix, queries, nq, logits, Buffers{}, stream));
+    // one kernel, no activations to hold: as many rows at once as a launch takes,
+    // in even parts (a short last one would not go in one kernel)
+    const int64_t parts = (nq + nr::ENCODE_ROWS - 1) / nr::ENCODE_ROWS;
+    const int64_t per = (nq + parts - 1) / parts;
+    for (int64_t q0 = 0; q0 < nq; q0 += per) {
+      const int64_t n = std::min(nq - q0, per);
+      HIP_OK(run_encode(ix, (const char *)queries + q0 * ix->d.d * elem_size(ix), n,
+                        logits + q0 * ix->d.b, Buffers{}, stream));
+    }
     return NR_OK;
   }
   Buffers B;

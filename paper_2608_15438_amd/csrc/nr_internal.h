@@ -20,6 +20,9 @@ constexpr int MAX_TILES_PER_QUERY = NR_MAX_TILES_PER_QUERY;  // refinement tiles
 constexpr int TILE_MIN_ROWS = NR_TILE_MIN_ROWS;  // smallest refinement tile
 constexpr int STAGE_CLUSTERS = 128;       // clusters staged in LDS per refinement wave
 constexpr int64_t QUERY_CHUNK = 16384;    // queries per internal launch sequence
+// rows per launch of an encoder that holds no activations: a one-layer encoder
+// takes 8 threads a row, and a launch fewer than 2^32
+constexpr int64_t ENCODE_ROWS = (int64_t)1 << 26;
 #ifndef NR_OWN_TILE_MIN_ROWS
 #define NR_OWN_TILE_MIN_ROWS 2048
 #endif

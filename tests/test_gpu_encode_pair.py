@@ -47,3 +47,20 @@ def test_pair_logits(u8, d, h, b, m):
     # rows do not depend on the batch they come in
     assert torch.equal(got[m // 2:m // 2 + 1], ix.nr_encode(x[m // 2:m // 2 + 1].clone()))
     ix.close()
+
+
+@pytest.mark.parametrize("widths,m", [((16, 3), (1 << 29) + 77), ((16, 4, 2), (1 << 30) + 77)])
+def test_more_rows_than_one_launch(widths, m):
+    # 32 rows of a one-layer encoder, or 64 of a two-layer one, take a block of
+    # 256 threads; a launch takes fewer than 2^32
+    rng = np.random.default_rng(len(widths))
+    W = [rng.standard_normal((o, i)).astype(np.float32) for i, o in zip(widths, widths[1:])]
+    bias = [rng.standard_normal(o).astype(np.float32) for o in widths[1:]]
+    ix = NR.Index.encoder_only(IB.Encoder(W, bias, 1.0), NR.NR_U8)
+    x = torch.empty((m, 16), dtype=torch.uint8, device="cuda")
+    x.random_(0, 256, generator=torch.Generator(device="cuda").manual_seed(1))
+    got = ix.nr_encode(x)
+    step = 1 << 24
+    for i in list(range(0, m, 7 * step)) + [m - 1000]:
+        assert torch.equal(got[i:i + step], ix.nr_encode(x[i:i + step])), i
+    ix.close()
