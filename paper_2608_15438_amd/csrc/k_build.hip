@@ -367,6 +367,13 @@ constexpr int MID_ROWS = BT;      // and by a block of BT threads
 constexpr int BIG = 1024;
 constexpr int LIST_GRID = 2048;   // blocks that walk a list
 
+// Kernels with a wave per item are launched over WAVES_MAX items at a time (a
+// launch takes fewer than 2^32 threads); a wave's item is `first` + its number
+constexpr int64_t WAVES_MAX = (int64_t)1 << 24;
+__device__ __forceinline__ int64_t wave_number() {
+  return (int64_t)blockIdx.x * (BT / WAVE) + threadIdx.x / WAVE;
+}
+
 struct SizeLists {
   uint32_t *mid, *big;
   uint32_t *count;  // [2], zero before the wave kernel
@@ -379,9 +386,9 @@ __device__ __forceinline__ void list_bucket(const SizeLists &l, int64_t m, uint3
 
 // the ids of every bucket ascending: one wave per bucket of at most 64 rows
 __global__ void __launch_bounds__(BT) k_build_sort_wave(uint32_t *ids, const uint64_t *boff,
-                                                        int64_t nb, SizeLists l) {
+                                                        int64_t nb, SizeLists l, int64_t first) {
   const int lane = lane_id();
-  const int64_t c = (int64_t)blockIdx.x * (BT / WAVE) + threadIdx.x / WAVE;
+  const int64_t c = first + wave_number();
   if (c >= nb) return;
   const uint64_t s0 = boff[c];
   const int64_t m = (int64_t)(boff[c + 1] - s0);
@@ -484,9 +491,10 @@ __device__ __forceinline__ double sqd(const float (&x)[BP], const float (&c)[BP]
 // k-means++ of a bucket of at most 64 rows by one wave, a sample member per
 // lane: its row and D^2 stay in registers, the running weights are a wave scan
 template <int BP>
-__global__ void __launch_bounds__(BT) k_build_seed_wave(KmArgs a, SizeLists l) {
+__global__ void __launch_bounds__(BT) k_build_seed_wave(KmArgs a, SizeLists l,
+                                                        int64_t first) {
   const int lane = lane_id();
-  const int64_t mi = (int64_t)blockIdx.x * (BT / WAVE) + threadIdx.x / WAVE;
+  const int64_t mi = first + wave_number();
   if (mi >= a.n_multi) return;
   const uint32_t code = a.mlist[mi];
   const uint64_t s0 = a.boff[code];
@@ -673,9 +681,9 @@ __global__ void __launch_bounds__(NT) k_build_seed_list(KmArgs a, const uint32_t
 // the waves that take a slot each start from one load
 __global__ void __launch_bounds__(BT) k_build_slots(const uint32_t *kb, const uint64_t *kbpre,
                                                     const uint64_t *boff, int64_t nb,
-                                                    int64_t slots, uint4 *slot) {
+                                                    int64_t slots, uint4 *slot, int64_t first) {
   const int lane = lane_id();
-  const int64_t w0 = (int64_t)blockIdx.x * (BT / WAVE) + threadIdx.x / WAVE;
+  const int64_t w0 = first + wave_number();
   const int64_t c = w0 * WAVE + lane;
   const uint32_t k = c < nb ? kb[c] : 0u;
   const uint64_t p = c < nb ? kbpre[c] : 0ull;
@@ -696,9 +704,9 @@ __global__ void __launch_bounds__(BT) k_build_slots(const uint32_t *kb, const ui
 
 // the multi-cluster buckets' members, 64 to a tile; 64 buckets per wave, one
 // atomic each
-__global__ void __launch_bounds__(BT) k_build_tiles(KmArgs a) {
+__global__ void __launch_bounds__(BT) k_build_tiles(KmArgs a, int64_t first) {
   const int lane = lane_id();
-  const int64_t mi = ((int64_t)blockIdx.x * (BT / WAVE) + threadIdx.x / WAVE) * WAVE + lane;
+  const int64_t mi = (first + wave_number()) * WAVE + lane;
   uint32_t code = 0, nt = 0;
   if (mi < a.n_multi) {
     code = a.mlist[mi];
@@ -724,10 +732,11 @@ __global__ void __launch_bounds__(BT) k_build_tiles(KmArgs a) {
 // pass.  A bucket in which the last pass changed no label is at rest: its
 // centres and labels stay as they are.
 template <int BP>
-__global__ void __launch_bounds__(BT) k_build_assign(KmArgs a, uint32_t pass) {
+__global__ void __launch_bounds__(BT) k_build_assign(KmArgs a, uint32_t pass,
+                                                     int64_t first) {
   const int lane = lane_id();
-  const uint32_t t = (uint32_t)__builtin_amdgcn_readfirstlane(
-      (int)(blockIdx.x * (BT / WAVE) + threadIdx.x / WAVE));
+  const uint32_t t =
+      (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(first + wave_number()));
   if (t >= *a.ntile) return;
   const uint2 tl = a.tile[t];
   const uint32_t code = (uint32_t)__builtin_amdgcn_readfirstlane((int)tl.x);
@@ -793,9 +802,10 @@ __device__ __forceinline__ void ordered_add(double &sum, const float *lg, int b,
 
 // Lloyd, second half: one wave per slot finds its members 64 labels at a time
 // and adds them in id order
-__global__ void __launch_bounds__(BT) k_build_update(KmArgs a, uint32_t pass, int last) {
+__global__ void __launch_bounds__(BT) k_build_update(KmArgs a, uint32_t pass, int last,
+                                                     int64_t first) {
   const int lane = lane_id();
-  const int64_t sl = (int64_t)blockIdx.x * (BT / WAVE) + threadIdx.x / WAVE;
+  const int64_t sl = first + wave_number();
   if (sl >= a.slots) return;
   const uint4 rec = a.slot[sl];
   const uint32_t code = rec.w, m = rec.y, k = rec.z;
@@ -854,9 +864,9 @@ struct FinArgs {
 // one wave per slot: its cluster's rows in (cluster, id) order, size and
 // centroid.  Empty slots are dropped, so a slot's cluster number and first row
 // come from the counts of its bucket's earlier slots
-__global__ void __launch_bounds__(BT) k_build_finish(FinArgs a) {
+__global__ void __launch_bounds__(BT) k_build_finish(FinArgs a, int64_t first) {
   const int lane = lane_id();
-  const int64_t sl = (int64_t)blockIdx.x * (BT / WAVE) + threadIdx.x / WAVE;
+  const int64_t sl = first + wave_number();
   if (sl >= a.slots) return;
   const uint4 rec = a.slot[sl];
   const uint32_t c = rec.w, m = rec.y, k = rec.z;
@@ -995,15 +1005,38 @@ static dim3 list_grid(int64_t items) {
   return dim3((unsigned)(items < LIST_GRID ? (items > 0 ? items : 1) : LIST_GRID));
 }
 
+// launch(grid, first) over `items` waves, WAVES_MAX at a time
+template <class Launch>
+static void for_waves(int64_t items, Launch launch) {
+  constexpr int64_t wpb = BT / WAVE;
+  for (int64_t first = 0; first < items; first += WAVES_MAX) {
+    const int64_t n = items - first < WAVES_MAX ? items - first : WAVES_MAX;
+    launch(dim3((unsigned)((n + wpb - 1) / wpb)), first);
+  }
+}
+
 template <int BP>
 static void launch_seeds(const KmArgs &k, const SizeLists &l, int64_t n, hipStream_t s) {
-  const int64_t wpb = BT / WAVE;
-  hipLaunchKernelGGL(k_build_seed_wave<BP>, dim3((unsigned)((k.n_multi + wpb - 1) / wpb)),
-                     dim3(BT), 0, s, k, l);
+  for_waves(k.n_multi, [&](dim3 g, int64_t first) {
+    hipLaunchKernelGGL(k_build_seed_wave<BP>, g, dim3(BT), 0, s, k, l, first);
+  });
   hipLaunchKernelGGL((k_build_seed_list<BT, BP>), list_grid(k.n_multi), dim3(BT), 0, s, k, l.mid,
                      l.count);
   hipLaunchKernelGGL((k_build_seed_list<BIG, BP>), list_grid(n / MID_ROWS), dim3(BIG), 0, s, k,
                      l.big, l.count + 1);
+}
+
+static void launch_assign(const KmArgs &k, uint32_t pass, dim3 g, int64_t first, hipStream_t s) {
+  switch (k.bp / 4) {
+    case 1: hipLaunchKernelGGL(k_build_assign<4>, g, dim3(BT), 0, s, k, pass, first); break;
+    case 2: hipLaunchKernelGGL(k_build_assign<8>, g, dim3(BT), 0, s, k, pass, first); break;
+    case 3: hipLaunchKernelGGL(k_build_assign<12>, g, dim3(BT), 0, s, k, pass, first); break;
+    case 4: hipLaunchKernelGGL(k_build_assign<16>, g, dim3(BT), 0, s, k, pass, first); break;
+    case 5: hipLaunchKernelGGL(k_build_assign<20>, g, dim3(BT), 0, s, k, pass, first); break;
+    case 6: hipLaunchKernelGGL(k_build_assign<24>, g, dim3(BT), 0, s, k, pass, first); break;
+    case 7: hipLaunchKernelGGL(k_build_assign<28>, g, dim3(BT), 0, s, k, pass, first); break;
+    default: hipLaunchKernelGGL(k_build_assign<32>, g, dim3(BT), 0, s, k, pass, first); break;
+  }
 }
 
 hipError_t run_build_index(const BuildArgs &A, hipStream_t s) {
@@ -1016,19 +1049,21 @@ hipError_t run_build_index(const BuildArgs &A, hipStream_t s) {
   if ((e = launch_fill_i32((int32_t *)A.cursor, nb, 0, s)) != hipSuccess) return e;
   hipLaunchKernelGGL(k_build_scatter, grid_for(n), dim3(BT), 0, s, A.codes, n, A.boff, A.cursor,
                      A.ids);
-  const int64_t wpb = BT / WAVE;  // buckets, slots or tiles per block, a wave each
-  auto waves = [&](int64_t items) { return dim3((unsigned)((items + wpb - 1) / wpb)); };
   const SizeLists l{A.list_mid, A.list_big, A.counts};
   if ((e = launch_fill_i32((int32_t *)A.counts, 5, 0, s)) != hipSuccess) return e;
-  hipLaunchKernelGGL(k_build_sort_wave, waves(nb), dim3(BT), 0, s, A.ids, A.boff, nb, l);
+  for_waves(nb, [&](dim3 g, int64_t first) {
+    hipLaunchKernelGGL(k_build_sort_wave, g, dim3(BT), 0, s, A.ids, A.boff, nb, l, first);
+  });
   hipLaunchKernelGGL(k_build_sort_list<BT>, list_grid(nb), dim3(BT), 0, s, A.ids, A.boff,
                      A.ids_tmp, l.mid, l.count);
   hipLaunchKernelGGL(k_build_sort_list<BIG>, list_grid(n / MID_ROWS), dim3(BIG), 0, s, A.ids,
                      A.boff, A.ids_tmp, l.big, l.count + 1);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if ((e = launch_fill_i32((int32_t *)A.slot, 4 * A.slots, 0, s)) != hipSuccess) return e;
-  hipLaunchKernelGGL(k_build_slots, waves((nb + WAVE - 1) / WAVE), dim3(BT), 0, s, A.kb, A.kbpre,
-                     A.boff, nb, A.slots, A.slot);
+  for_waves((nb + WAVE - 1) / WAVE, [&](dim3 g, int64_t first) {
+    hipLaunchKernelGGL(k_build_slots, g, dim3(BT), 0, s, A.kb, A.kbpre, A.boff, nb, A.slots, A.slot,
+                       first);
+  });
   // k-means of the multi-cluster buckets
   if ((e = launch_fill_i32((int32_t *)A.nkept, nb, 0, s)) != hipSuccess) return e;
   if (A.n_multi > 0) {
@@ -1059,7 +1094,9 @@ hipError_t run_build_index(const BuildArgs &A, hipStream_t s) {
     k.ntile = A.counts + 4;
     k.nkept = A.nkept;
     const SizeLists lm{A.list_mid, A.list_big, A.counts + 2};
-    hipLaunchKernelGGL(k_build_tiles, waves((A.n_multi + WAVE - 1) / WAVE), dim3(BT), 0, s, k);
+    for_waves((A.n_multi + WAVE - 1) / WAVE, [&](dim3 g, int64_t first) {
+      hipLaunchKernelGGL(k_build_tiles, g, dim3(BT), 0, s, k, first);
+    });
     switch ((A.b + 7) / 8) {
       case 1: launch_seeds<8>(k, lm, n, s); break;
       case 2: launch_seeds<16>(k, lm, n, s); break;
@@ -1067,20 +1104,14 @@ hipError_t run_build_index(const BuildArgs &A, hipStream_t s) {
       default: launch_seeds<32>(k, lm, n, s); break;
     }
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    const dim3 ga = waves(n / WAVE + A.n_multi);
     for (int it = 1; it <= A.lloyd; ++it) {
-      switch (k.bp / 4) {
-        case 1: hipLaunchKernelGGL(k_build_assign<4>, ga, dim3(BT), 0, s, k, (uint32_t)it); break;
-        case 2: hipLaunchKernelGGL(k_build_assign<8>, ga, dim3(BT), 0, s, k, (uint32_t)it); break;
-        case 3: hipLaunchKernelGGL(k_build_assign<12>, ga, dim3(BT), 0, s, k, (uint32_t)it); break;
-        case 4: hipLaunchKernelGGL(k_build_assign<16>, ga, dim3(BT), 0, s, k, (uint32_t)it); break;
-        case 5: hipLaunchKernelGGL(k_build_assign<20>, ga, dim3(BT), 0, s, k, (uint32_t)it); break;
-        case 6: hipLaunchKernelGGL(k_build_assign<24>, ga, dim3(BT), 0, s, k, (uint32_t)it); break;
-        case 7: hipLaunchKernelGGL(k_build_assign<28>, ga, dim3(BT), 0, s, k, (uint32_t)it); break;
-        default: hipLaunchKernelGGL(k_build_assign<32>, ga, dim3(BT), 0, s, k, (uint32_t)it); break;
-      }
-      hipLaunchKernelGGL(k_build_update, waves(A.slots), dim3(BT), 0, s, k, (uint32_t)it,
-                         it == A.lloyd ? 1 : 0);
+      for_waves(n / WAVE + A.n_multi, [&](dim3 g, int64_t first) {
+        launch_assign(k, (uint32_t)it, g, first, s);
+      });
+      for_waves(A.slots, [&](dim3 g, int64_t first) {
+        hipLaunchKernelGGL(k_build_update, g, dim3(BT), 0, s, k, (uint32_t)it,
+                           it == A.lloyd ? 1 : 0, first);
+      });
     }
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
@@ -1103,7 +1134,9 @@ hipError_t run_build_index(const BuildArgs &A, hipStream_t s) {
   f.row_ids = A.row_ids;
   f.csize = A.csize;
   f.centroids = A.centroids;
-  hipLaunchKernelGGL(k_build_finish, waves(A.slots), dim3(BT), 0, s, f);
+  for_waves(A.slots, [&](dim3 g, int64_t first) {
+    hipLaunchKernelGGL(k_build_finish, g, dim3(BT), 0, s, f, first);
+  });
   return hipGetLastError();
 }
 

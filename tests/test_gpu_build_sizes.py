@@ -23,6 +23,11 @@ LARGE = [4096, 4097, 9000]
 @pytest.mark.parametrize("b,sizes,cap", [(4, SIZES, 20), (9, SIZES + LARGE, 200), (16, SIZES, 3),
                                          (17, SIZES, 30), (12, SIZES + LARGE, 1 << 20)])
 def test_build_bucket_sizes(b, sizes, cap):
+    check_build(b, sizes, cap)
+
+
+def check_build(b, sizes, cap, most=0):
+    """`most`: the bound on the clusters passed on (0: the plan's)."""
     rng = np.random.default_rng(b)
     n = sum(sizes)
     code = rng.choice(1 << b, len(sizes), replace=False)
@@ -45,7 +50,7 @@ def test_build_bucket_sizes(b, sizes, cap):
     NR.nr_build_codes(d, tau, codes, cnt)
     assert np.array_equal(codes.cpu().numpy(), of)
     kb, mlist, info = NR.nr_build_plan(cnt, n, b, NR.NR_CLUSTER_CAPACITY, cap)
-    nm, kmax, mc = int(info.n_multi), max(2, int(info.kmax)), int(info.max_clusters)
+    nm, kmax, mc = int(info.n_multi), max(2, int(info.kmax)), max(most, int(info.max_clusters))
     u = np.zeros((1, kmax))
     if nm:
         u = G.uniform01(w.seed("sample"), mlist[:nm].cpu().numpy().astype(np.int64), kmax,
@@ -65,6 +70,13 @@ def test_build_bucket_sizes(b, sizes, cap):
     assert np.array_equal(cl[:nc + 1].cpu().numpy(), np.asarray(ref.cl_off, np.int64))
     assert np.array_equal(row_ids.cpu().numpy(), np.asarray(ref.row_ids))
     assert np.allclose(cent[:nc].cpu().numpy(), ref.centroids, rtol=2.0 ** -23, atol=0)
+
+
+@pytest.mark.parametrize("b,most", [(26, 0), (27, 0), (5, (1 << 26) + 9)])
+def test_build_more_waves_than_one_launch(b, most):
+    # a wave per bucket (2^b) and per cluster slot (the caller's bound on the
+    # clusters); a launch takes fewer than 2^26 waves
+    check_build(b, SIZES, 20, most)
 
 
 @pytest.mark.parametrize("ns,b", [(1, 5), (2, 30), (8191, 16), (8192, 16), (8193, 7), (50_001, 30),
