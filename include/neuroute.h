@@ -297,8 +297,10 @@ nr_status nr_lsim_grad(const float *d2_emb, const float *lat, int64_t B, int32_t
 /* tau_emb of a batch without a copy to the host: nr_pair_quantile writes to
  * out (DEVICE fp64 [1]) the q-quantile (linear interpolation, the rank in
  * fp32) of the first `limit` (at most 2^24) off-diagonal elements of d2_emb
- * in row order; ws: DEVICE scratch of nr_pair_quantile_ws() bytes.
- * nr_lsim_grad_at is nr_lsim_grad with tau_emb = sqrt(*tau_sq). */
+ * in row order (values >= 0; NaN if one of them is NaN); ws: DEVICE scratch of
+ * nr_pair_quantile_ws() bytes.  nr_lsim_grad_at is nr_lsim_grad with tau_emb =
+ * sqrt(*tau_sq), which the call cannot check: the caller rejects a step whose
+ * *tau_sq turns out not to be finite. */
 size_t nr_pair_quantile_ws(void);
 nr_status nr_pair_quantile(const float *d2_emb, int64_t B, int64_t limit, float q, void *ws,
                            double *out, hipStream_t stream);

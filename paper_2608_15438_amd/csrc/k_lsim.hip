@@ -206,6 +206,7 @@ struct QuantState {
   uint32_t prefix;     // digits picked so far
   uint32_t rank;       // rank among the keys of that prefix
   uint32_t above;      // least key past the prefix's range (last pass)
+  uint32_t nan;        // whether an element is NaN (first pass): then so is the quantile
 };
 
 __global__ void __launch_bounds__(256) k_quant_init(QuantState *st, uint32_t rank) {
@@ -215,6 +216,7 @@ __global__ void __launch_bounds__(256) k_quant_init(QuantState *st, uint32_t ran
     st->prefix = 0;
     st->rank = rank;
     st->above = 0xffffffffu;
+    st->nan = 0;
   }
 }
 
@@ -233,9 +235,11 @@ __global__ void __launch_bounds__(256) k_pair_quantile(const float *d2, int64_t 
   __syncthreads();
   const uint32_t prefix = st->prefix;
   uint32_t above = 0xffffffffu;
+  bool nan = false;
   auto count = [&](uint32_t k, bool in) {
     if (PASS == 0) {
       if (in) atomicAdd(&h[wv][k >> SHIFT], 1u);
+      nan |= in && k > 0x7f800000u;
     } else {
       const uint32_t top = k >> (SHIFT + 10);
       if (in && top == prefix) atomicAdd(&h[wv][(k >> SHIFT) & 1023u], 1u);
@@ -287,6 +291,7 @@ __global__ void __launch_bounds__(256) k_pair_quantile(const float *d2, int64_t 
     const uint32_t c = h[0][i] + h[1][i] + h[2][i] + h[3][i];
     if (c) atomicAdd(&st->hist[PASS][i], c);
   }
+  if (PASS == 0 && ballot(nan) && lane == 0) atomicOr(&st->nan, 1u);
   if (PASS == 2) {
     for (int m = 1; m < WAVE; m <<= 1) {
       const uint32_t o = (uint32_t)__shfl_xor((int)above, m);
@@ -361,7 +366,7 @@ __global__ void __launch_bounds__(256) k_quant_pick(QuantState *st, float w, int
     const float a = __uint_as_float(lo), b = __uint_as_float(hi);
     // the interpolation of torch.quantile (its lerp)
     const float d = b - a;
-    *out = (double)(w < 0.5f ? fmaf(w, d, a) : fmaf(-d, 1.0f - w, b));
+    *out = st->nan ? (double)NAN : (double)(w < 0.5f ? fmaf(w, d, a) : fmaf(-d, 1.0f - w, b));
   }
 }
 

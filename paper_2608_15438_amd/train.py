@@ -97,7 +97,10 @@ def lsim_loss_gpu(x: torch.Tensor, lat: torch.Tensor, gamma: float,
     grad = NR.nr_lsim_grad_at(d2, l32, gr, stats)
     loss = _LsimGpu.apply(lat, stats[:2], grad)
     _, cnt, tau_sq = stats.tolist()
-    return loss, math.sqrt(tau_sq), cnt / (B * (B - 1))
+    tau_emb = math.sqrt(tau_sq)
+    if not math.isfinite(tau_emb):
+        NR.nr_lsim_grad(d2, l32, gr, tau_emb)  # its error for a tau_emb that is not finite
+    return loss, tau_emb, cnt / (B * (B - 1))
 
 
 class _Mlp(torch.nn.Module):

@@ -112,3 +112,34 @@ def test_loss_reads_tau_on_the_device():
         TR.lsim_loss_gpu(x[:1], lat[:1], 0.6)
     with pytest.raises(RuntimeError):
         TR.lsim_loss_gpu(x, lat, 0.6, quantile=1.5)
+
+
+def test_loss_rejects_a_non_finite_tau():
+    # distances that overflow at the quantile: an error, as when tau_emb is given
+    g = torch.Generator(device="cuda").manual_seed(4)
+    lat = torch.randn((128, 8), generator=g, device="cuda", requires_grad=True)
+    x = torch.full((128, 16), 1e25, device="cuda")
+    x[::2] *= -1                                     # half of the pairs at infinity
+    for q in (0.9, 1.0):
+        with pytest.raises(NR.NRError) as e:
+            TR.lsim_loss_gpu(x, lat, 0.6, quantile=q)
+        assert e.value.status == NR.NR_EINVAL
+    assert math.isfinite(TR.lsim_loss_gpu(x, lat, 0.6, quantile=0.1)[1])
+    # one row out of range: the pairs below the quantile are not concerned
+    x = torch.randn((128, 16), generator=g, device="cuda")
+    x[5] = 1e25
+    assert math.isfinite(TR.lsim_loss_gpu(x, lat, 0.6, quantile=0.0)[1])
+
+
+@pytest.mark.parametrize("at,limit", [((0, 1), 1 << 24), ((40, 3), 1 << 24), ((69, 68), 1 << 24),
+                                      ((5, 5), 1 << 24), ((69, 0), 100)])
+def test_pair_quantile_nan(at, limit):
+    # a NaN among the elements makes the quantile NaN, as torch.quantile's; on
+    # the diagonal or past the limit it is not among them
+    g = torch.Generator(device="cuda").manual_seed(2)
+    d2 = torch.rand((70, 70), generator=g, device="cuda")
+    d2[at] = float("nan")
+    off = d2[~torch.eye(70, dtype=torch.bool, device="cuda")][:limit]
+    for q in (0.0, 0.005, 1.0):
+        got, want = float(NR.nr_pair_quantile(d2, q, limit)), float(torch.quantile(off, q))
+        assert got == want or (math.isnan(got) and math.isnan(want)), (q, got, want)
