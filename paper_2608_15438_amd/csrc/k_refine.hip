@@ -700,8 +700,9 @@ __global__ void __launch_bounds__(256) k_merge(MergeArgs a) {
     const bool have = best != ~0ull;
     const uint32_t key = (uint32_t)(best >> 32);
     a.out_ids[q * k + lane] = have ? (int64_t)(uint32_t)best : -1;
+    // (the shared schedule's seed keeps its keys: a uint8 row's is exact, fp32 is not past 2^24)
     a.out_dists[q * k + lane] =
-        have ? (a.is_u8 ? (float)key : __uint_as_float(key)) : INFINITY;
+        have ? (a.is_u8 && !a.qrec ? (float)key : __uint_as_float(key)) : INFINITY;
   }
   // The scan's record of the query: its bound (the k-th key of the seed pass,
   // or all ones while that list is short), the bound the head test compares

@@ -1280,8 +1280,8 @@ __global__ void __launch_bounds__(256) k_shared_merge(SharedArgs a) {
   uint64_t best = ~0ull;
   if (lane < k) {
     const int64_t id = a.own_ids[q * k + lane];
-    const float d = a.own_dists[q * k + lane];
-    if (id >= 0) best = ((uint64_t)(a.is_u8 ? (uint32_t)d : __float_as_uint(d)) << 32) | (uint32_t)id;
+    const uint32_t key = __float_as_uint(a.own_dists[q * k + lane]);
+    if (id >= 0) best = ((uint64_t)key << 32) | (uint32_t)id;
   }
   // survivors: the query's own slots, then its pooled ones; four chunks of
   // 64 are loaded per round, ids only for keys that can still enter; a chunk

@@ -267,7 +267,8 @@ struct MergeArgs {
   float *out_dists;
   int32_t *qstats;
   const int32_t *qmask;  // only queries with qmask[q] != 0 are written, may be null
-  uint4 *qrec;           // [nq] the shared scan's record of each query, may be null
+  uint4 *qrec;           // [nq] the shared scan's record of each query, may be null; with it,
+                         // out_dists gets the keys' bits
   const uint2 *qnorm;    // [nq] uint8 rows, with qrec
 };
 
@@ -295,7 +296,7 @@ struct SharedArgs {
   int32_t *tile_off;          // [nq + 1] tiles of the own pass ([nq]: how many)
   int32_t *own_counter;       // [TILE_COUNTERS x TILE_COUNTER_STRIDE] of the own pass
   const int64_t *own_ids;     // [nq x k] top-k of the own pass (sorted)
-  const float *own_dists;
+  const float *own_dists;     // its keys (fp32 distances, or the bits of uint8 rows' whole ones)
   uint32_t *own_rows;         // [nq] copy of rtot kept for diagnostics
   uint32_t *hist;             // [n_clusters + 1] pairs per cluster past the leading clusters
   uint32_t *pair_rank;        // [nq x cap] rank of each counted pair among its cluster's pairs

@@ -86,6 +86,26 @@ def test_shared_equals_per_query_large_scan():
     ix.close()
 
 
+@pytest.mark.parametrize("d", [272, 528, 1536])
+@pytest.mark.parametrize("k", [1, 10, 64])
+def test_uint8_keys_past_2_24(d, k):
+    # squared distances of whole numbers that fp32 no longer tells apart: both
+    # schedules order rows by the exact ones
+    from paper_2608_15438_amd import neuroute as NR
+    n, nq = 6000, 600
+    ix, rows = make_index(n, d, 5, NR.NR_U8, 0, seed=d)
+    g = torch.Generator(device="cuda").manual_seed(k)
+    rows.copy_(torch.randint(0, 2, (n, d), generator=g, device="cuda"))
+    q = torch.randint(253, 256, (nq, d), generator=g, device="cuda").to(torch.uint8)
+    ids, dists = both(ix, q, k, 32, 5, shared_seed_rows=64)
+    pos = torch.empty(n, dtype=torch.int64, device="cuda")
+    pos[ix.dev[1]] = torch.arange(n, device="cuda")
+    dist = (q[:, None].long() - rows[pos[ids]].long()).square().sum(-1)
+    assert dist.min() > 1 << 24
+    key = dist * (1 << 20) + ids
+    assert (key[:, 1:] > key[:, :-1]).all()
+    ix.close()
+
 
 @pytest.mark.parametrize("nq", [1, 5, 48, 300, 700])
 @pytest.mark.parametrize("k", [1, 9, 32, 33, 64])
