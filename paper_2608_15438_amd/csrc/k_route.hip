@@ -59,6 +59,12 @@ __device__ __forceinline__ float margin_dev(int m, float kx, float ky, float ks,
   return v;
 }
 
+// the keys of distances d <= theta (d >= 0) are those below this: none where
+// the margin takes theta below zero
+__device__ __forceinline__ uint64_t gate_cut(float theta) {
+  return theta < 0.0f ? 0ull : ((uint64_t)__float_as_uint(theta + 0.0f) + 1ull) << 32;
+}
+
 // minimum over the wave with DPP moves inside each row of 16 lanes (pairs,
 // quads, half rows, rows) and the four row minima read from lanes 0, 16, 32
 // and 48; exact, like any order of fminf over finite values and +inf
@@ -330,7 +336,7 @@ __device__ __forceinline__ void route_query(const RouteArgs &a, const int64_t q)
     const float am = a.alpha_front * M;
     const float theta_f = d_min + am;
     const bool valid = lane < nb && d <= theta;
-    const uint64_t cut = ((uint64_t)__float_as_uint(theta) + 1ull) << 32;
+    const uint64_t cut = gate_cut(theta);
     if (fastm) {
       const uint64_t vm = ballot(valid);
       const int nvf = popc64(vm);
@@ -510,7 +516,7 @@ __device__ __forceinline__ void route_query(const RouteArgs &a, const int64_t q)
       }
       __builtin_amdgcn_wave_barrier();
     }
-    cut_last = ((uint64_t)__float_as_uint(theta) + 1ull) << 32;
+    cut_last = gate_cut(theta);
     if (!direct) {  // the heap could fill: from the start, batch by batch
       npool = ndir = p = 0;
       d_min = INFINITY;
