@@ -42,11 +42,18 @@ __device__ __forceinline__ float4 enc_load_w4(const EncodeLayerArgs &a, int n, i
   return *reinterpret_cast<const float4 *>(a.W + (int64_t)n * a.K + kg);
 }
 
-// K-tiles of 16 are kept by row in LDS, KS floats apart, k = 4 s + g at slot
-// 4 g + s: lane l of a 16x16x4 block takes k = l / 16 of each of four steps, so
-// its operands for all four are one 16-byte read, and reads and writes fall on
-// different banks (by k, with a read per operand and up to three lanes on a
-// bank: 1M rows of 128 -> 256 -> 24 988 us, so 966; 10,000 of 1536 -> 512 the same).
+// Two orders of a K-tile of 16 in LDS.  By row: KS floats apart, k = 4 s + g at
+// slot 4 g + s, so that the operands of lane l of a 16x16x4 block (k = l / 16 of
+// each of four steps) are one 16-byte read, and reads and writes fall on
+// different banks.  By k: a row of operands per k, a read per operand, up to
+// three lanes on a bank, but a K-tile's reads spread over its steps.  Layers by
+// row / by k, us: 32 x 64 tiles 1 to 9 % faster by row (16,384 x 256 -> 64 17.3 /
+// 18.8, 32,768 uint8 rows of 1536 -> 128 185 / 199); 64 x 64 tiles, two layers K -> N
+// -> 16, fp32 slower by row (16,384 rows of 512 -> 512 114 / 105, 512 -> 1024 217 / 198,
+// 1536 -> 512 283 / 258), uint8 rows faster for long K and N up to 512 (8,192 of
+// 1536 -> 512 155 / 166, 16,384 of 1536 -> 256 146 / 154; but 12,288 of 768 -> 1024
+// 242 / 223); code layers (32 x 32) slower by row from K = 512 on (12,288 rows of 64 ->
+// 1024 -> 16 69 / 66).
 // Tiles of 128 x 64, 64 x 128 and 128 x 128 are no faster (5, 4 and 24 % slower
 // for the 1536-d encoder)
 constexpr int KS = 20;
@@ -72,7 +79,7 @@ __device__ __forceinline__ void enc_ktile(v4f (&acc)[MI][NJ], const float *A, co
       }
 }
 
-template <int BM, int BN, int BK, bool VEC>
+template <int BM, int BN, int BK, bool VEC, bool ROWS>
 __global__ void __launch_bounds__(256) k_encode_layer(EncodeLayerArgs a) {
   constexpr int MI = BM / 32, NJ = BN / 32;  // 16 x 16 blocks per wave
   constexpr int VW = VEC ? 4 : 1;            // elements per load
@@ -80,8 +87,11 @@ __global__ void __launch_bounds__(256) k_encode_layer(EncodeLayerArgs a) {
   constexpr int PA = (LA + 255) / 256, PW = (LW + 255) / 256;  // per thread (at most)
   static_assert(BK == 16 && BM % 32 == 0 && BN % 32 == 0, "whole MFMA blocks");
   // two K-tiles of A (activations) and W
-  __shared__ __attribute__((aligned(16))) float As[2][BM][KS];
-  __shared__ __attribute__((aligned(16))) float Ws[2][BN][KS];
+  __shared__ __attribute__((aligned(16))) float As[2][ROWS ? BM * KS : BK * (BM + 4)];
+  __shared__ __attribute__((aligned(16))) float Ws[2][ROWS ? BN * KS : BK * (BN + 4)];
+  auto at = [](int rows, int r, int k) {
+    return ROWS ? r * KS + enc_slot(k) : k * (rows + 4) + r;
+  };
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
   // tile of this block: the column tiles of one row tile are consecutive
@@ -143,7 +153,7 @@ __global__ void __launch_bounds__(256) k_encode_layer(EncodeLayerArgs a) {
       const int r = e / (BK / VW), kk = VW * (e % (BK / VW));
       if (LA % 256 != 0 && e >= LA) continue;
 #pragma unroll
-      for (int v = 0; v < VW; ++v) As[buf][r][enc_slot(kk + v)] = ra[u][v];
+      for (int v = 0; v < VW; ++v) As[buf][at(BM, r, kk + v)] = ra[u][v];
     }
 #pragma unroll
     for (int u = 0; u < PW; ++u) {
@@ -151,7 +161,7 @@ __global__ void __launch_bounds__(256) k_encode_layer(EncodeLayerArgs a) {
       const int r = e / (BK / VW), kk = VW * (e % (BK / VW));
       if (LW % 256 != 0 && e >= LW) continue;
 #pragma unroll
-      for (int v = 0; v < VW; ++v) Ws[buf][r][enc_slot(kk + v)] = rw[u][v];
+      for (int v = 0; v < VW; ++v) Ws[buf][at(BN, r, kk + v)] = rw[u][v];
     }
   };
   fetch(0);
@@ -161,7 +171,25 @@ __global__ void __launch_bounds__(256) k_encode_layer(EncodeLayerArgs a) {
   for (int k0 = 0; k0 < K; k0 += BK) {
     const bool more = k0 + BK < K;
     if (more) fetch(k0 + BK);
-    enc_ktile<MI, NJ>(acc, &As[buf][wm][0], &Ws[buf][wn][0]);
+    if constexpr (ROWS) {
+      enc_ktile<MI, NJ>(acc, &As[buf][wm * KS], &Ws[buf][wn * KS]);
+    } else {
+#pragma unroll
+      for (int kk = 0; kk < BK; kk += 4) {
+        // A operand of a 16x16x4 block: lane l holds row l % 16, k l / 16
+        const int kr = kk + (lane >> 4), c = lane & 15;
+        float av[MI], bv[NJ];
+#pragma unroll
+        for (int i = 0; i < MI; ++i) av[i] = As[buf][at(BM, wm + 16 * i + c, kr)];
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) bv[j] = Ws[buf][at(BN, wn + 16 * j + c, kr)];
+#pragma unroll
+        for (int i = 0; i < MI; ++i)
+#pragma unroll
+          for (int j = 0; j < NJ; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[i], bv[j], acc[i][j], 0, 0, 0);
+      }
+    }
     if (more) stash(buf ^ 1);
     __syncthreads();
     buf ^= 1;
@@ -376,7 +404,7 @@ hipError_t launch_encode_pair(const EncodeLayerArgs &a, const EncodeLayerArgs &z
   return hipGetLastError();
 }
 
-template <int BM, int BN, int BK>
+template <int BM, int BN, int BK, bool ROWS>
 static hipError_t launch_tile(const EncodeLayerArgs &a, hipStream_t s) {
   // row tiles in groups of 8 (one per XCD), each with all its column tiles
   const int64_t nm = (a.M + BM - 1) / BM, nn = (a.N + BN - 1) / BN;
@@ -385,9 +413,9 @@ static hipError_t launch_tile(const EncodeLayerArgs &a, hipStream_t s) {
   const bool vec = a.K % 4 == 0 && (reinterpret_cast<uintptr_t>(a.in) & 15) == 0 &&
                    (reinterpret_cast<uintptr_t>(a.W) & 15) == 0;
   if (vec)
-    hipLaunchKernelGGL((k_encode_layer<BM, BN, BK, true>), grid, dim3(256), 0, s, a);
+    hipLaunchKernelGGL((k_encode_layer<BM, BN, BK, true, ROWS>), grid, dim3(256), 0, s, a);
   else
-    hipLaunchKernelGGL((k_encode_layer<BM, BN, BK, false>), grid, dim3(256), 0, s, a);
+    hipLaunchKernelGGL((k_encode_layer<BM, BN, BK, false, ROWS>), grid, dim3(256), 0, s, a);
   return hipGetLastError();
 }
 
@@ -398,10 +426,13 @@ static hipError_t launch_tile(const EncodeLayerArgs &a, hipStream_t s) {
 // against 29 us with 64 x 64), 32 x 32 for the code layer (at most 32 outputs)
 hipError_t launch_encode_layer(const EncodeLayerArgs &a, hipStream_t s) {
   if (a.M <= 0) return hipSuccess;
-  if (a.N <= 32) return launch_tile<32, 32, 16>(a, s);
+  if (a.N <= 32)
+    return a.K < 512 ? launch_tile<32, 32, 16, true>(a, s) : launch_tile<32, 32, 16, false>(a, s);
   const int64_t tiles64 = ((a.M + 63) / 64) * ((a.N + 63) / 64);
-  if (tiles64 >= 1024) return launch_tile<64, 64, 16>(a, s);
-  return launch_tile<32, 64, 16>(a, s);
+  if (tiles64 >= 1024)
+    return a.in_u8 && a.K >= 512 && a.N <= 512 ? launch_tile<64, 64, 16, true>(a, s)
+                                               : launch_tile<64, 64, 16, false>(a, s);
+  return launch_tile<32, 64, 16, true>(a, s);
 }
 
 }  // namespace nr

@@ -64,3 +64,29 @@ def test_more_rows_than_one_launch(widths, m):
     for i in list(range(0, m, 7 * step)) + [m - 1000]:
         assert torch.equal(got[i:i + step], ix.nr_encode(x[i:i + step])), i
     ix.close()
+
+
+@pytest.mark.parametrize("u8,widths", [(True, (512, 448, 9)), (True, (528, 512, 16)),
+                                       (True, (496, 513, 16)), (False, (512, 520, 30)),
+                                       (False, (36, 511, 7)), (False, (1540, 448, 5))])
+def test_tiles_agree(u8, widths):
+    # 12,000 rows go in 64 x 64 tiles and 100 in 32 x 64 ones, in either order of
+    # their K-tiles: every logit is the same chain
+    rng = np.random.default_rng(widths[0])
+    W = [(rng.standard_normal((o, i)) / np.sqrt(i)).astype(np.float32)
+         for i, o in zip(widths, widths[1:])]
+    ix = NR.Index.encoder_only(IB.Encoder(W, [np.zeros(o, np.float32) for o in widths[1:]], 1.0),
+                               NR.NR_U8 if u8 else NR.NR_F32)
+    g = torch.Generator(device="cuda").manual_seed(1)
+    x = torch.rand((12_000, widths[0]), generator=g, device="cuda")
+    if u8:
+        x = (x * 256).to(torch.uint8)
+    got = ix.nr_encode(x)
+    for i in (0, 7777, 11_900):
+        assert torch.equal(got[i:i + 100], ix.nr_encode(x[i:i + 100].clone()))
+    h = (x.double() @ torch.from_numpy(W[0]).cuda().double().T).clamp_min(0)
+    w1 = torch.from_numpy(W[1]).cuda().double()
+    mag = (x.double().abs() @ torch.from_numpy(np.abs(W[0])).cuda().double().T) @ w1.abs().T
+    # two chains: at most one rounding of the magnitudes per product
+    assert ((got - h @ w1.T).abs() <= (widths[0] + widths[1] + 4) * 2.0 ** -24 * mag).all()
+    ix.close()
