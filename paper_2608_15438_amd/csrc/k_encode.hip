@@ -375,14 +375,33 @@ __global__ void __launch_bounds__(256) k_encode_pair(EncodeLayerArgs a, EncodeLa
 }
 
 // A pair goes to one kernel where the rows fill the chip by themselves: a block
-// walks all of the hidden layer, so few rows end with few blocks' chains, and a
-// block per tile of each layer is faster (whole searches behind 128 -> 256 -> 16:
-// one query 64 us with two kernels, 74 with one; 10,000 558 and 561).  From 16,384
-// rows on there are two blocks per CU; wide layers (longer chains) need more.
+// walks all of the hidden layer with three blocks to a CU (LDS), so few rows end
+// with few blocks' chains (65,536 rows are 1.3 rounds of the chip), and longer
+// chains (K) and more of them (N) hide less of their loads than the layer kernel's
+// seven blocks do.  Layers go 16,384 rows at a time, the last ones in a launch of
+// their own.  Two kernels / one, us, fp32 rows (uint8 rows in brackets), K -> N -> 16:
+//   16,384 rows: 128 -> 256 32 / 26, 256 -> 128 26 / 24, 512 -> 64 28 / 23, 256 -> 256 41 / 42
+//     (43 / 46), 512 -> 128 40 / 42, 128 -> 1024 90 / 91 (92 / 98)
+//   20,000 rows: 256 -> 256 60 / 51, 512 -> 128 60 / 49, 768 -> 64 62 / 37
+//   32,768 rows: 256 -> 512 139 / 125, 256 -> 1024 252 / 239 (but 50,000 406 / 439), 512 ->
+//     256 120 / 115 (but 40,000 (167 / 183))
+//   65,536 rows: 512 -> 256 233 / 203, 512 -> 512 411 / 403 (422 / 494), 768 -> 256 312 / 295
+//     (334 / 407), 768 -> 512 568 / 584 (100,000: 891 / 968), 1536 -> 128 373 / 313 (378 /
+//     400, 80,000: 449 / 406), 256 -> 1024 492 / 439, 768 -> 1024 1076 / 1160, 1536 -> 512 1018 / 1239 (1031 / 1439)
+//   131,072 rows: (512 -> 512 845 / 788), 512 -> 1024 1566 / 1461 (1591 / 1565), (768 -> 256
+//     669 / 630), (768 -> 512 1146 / 1235), 1536 -> 256 1128 / 1132, 1536 -> 512 2027 / 2233
 // 1M rows of 128 -> 256 -> 24: 1.96 ms in two kernels per 16,384 rows, 0.97 in
-// one (84 TFLOP/s of fp32)
-bool encode_pair(int64_t M, int K, int N, int NZ) {
-  return NZ <= 32 && M >= ((int64_t)K * N <= 65536 ? 16384 : 65536);
+// one (84 TFLOP/s of fp32).  One query behind 128 -> 256 -> 16: a whole search 64 us
+// with two kernels, 74 with one
+bool encode_pair(int64_t M, int K, int N, int NZ, bool u8) {
+  const int64_t KN = (int64_t)K * N;
+  if (NZ > 32) return false;
+  if (KN <= 32768 || (KN <= 65536 && (K <= 128 || N <= 64))) return M >= 16384;
+  if (KN <= 65536 || K <= 128) return M > 16384;
+  if (K <= 256) return M >= (KN <= 131072 ? 32768 : 65536);
+  if (KN <= 131072 || (!u8 && (KN <= 196608 || (K <= 768 && KN <= 262144)))) return M >= 65536;
+  if (KN <= 196608 && N <= 128) return M >= 73728;
+  return (K <= 512 || KN <= 196608) && M >= 131072;
 }
 
 hipError_t launch_encode_pair(const EncodeLayerArgs &a, const EncodeLayerArgs &z, hipStream_t s) {

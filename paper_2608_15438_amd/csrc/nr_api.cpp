@@ -402,7 +402,7 @@ hipError_t run_encode(const nr_index *ix, const void *q, int64_t nq, float *logi
     a.M = nq;
     a.K = ix->widths[l];
     a.N = ix->widths[l + 1];
-    if (l + 2 == L && nr::encode_pair(nq, a.K, a.N, ix->widths[L])) {
+    if (l + 2 == L && nr::encode_pair(nq, a.K, a.N, ix->widths[L], a.in_u8)) {
       prev = a;  // goes with the code layer
       continue;
     }
@@ -984,7 +984,8 @@ nr_status nr_encode(const nr_index *cix, const void *queries, int64_t nq, float 
   if (nq == 0) return NR_OK;
   if (!queries || !logits) return fail(NR_EINVAL, "queries and logits must not be NULL");
   const int L = (int)ix->widths.size() - 1;
-  if (L == 1 || (L == 2 && nr::encode_pair(nq, ix->widths[0], ix->widths[1], ix->widths[2]))) {
+  if (L == 1 || (L == 2 && nr::encode_pair(nq, ix->widths[0], ix->widths[1], ix->widths[2],
+                                                ix->d.dtype == NR_U8))) {
     // one kernel, no activations to hold: as many rows at once as a launch takes,
     // in even parts (a short last one would not go in one kernel)
     const int64_t parts = (nq + nr::ENCODE_ROWS - 1) / nr::ENCODE_ROWS;

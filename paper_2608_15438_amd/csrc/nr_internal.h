@@ -344,7 +344,7 @@ struct SharedArgs {
 hipError_t launch_encode_layer(const EncodeLayerArgs &a, hipStream_t s);
 // layers a (hidden, K -> N) and z (codes, N -> NZ) in one kernel: whether M
 // rows should go there, and the launch
-bool encode_pair(int64_t M, int K, int N, int NZ);
+bool encode_pair(int64_t M, int K, int N, int NZ, bool u8);
 hipError_t launch_encode_pair(const EncodeLayerArgs &a, const EncodeLayerArgs &z, hipStream_t s);
 hipError_t launch_probe(const ProbeArgs &a, hipStream_t s);
 constexpr int ROUTE_LIGHT_HEAP = 512;  // heap slots of the route's first pass
