@@ -640,8 +640,8 @@ hipError_t run_refine(const nr_index *ix, const void *q, int64_t nq, int k, cons
 // and the per-query schedule again for the queries whose survivors overflowed.
 // ev (may be null): after the own plan, own refinement, own merge, shared
 // prep, shared scan, shared merge.
-nr::SharedArgs shared_args(const nr_index *ix, const nr_params *p, const void *q, int64_t nq,
-                           int k, const uint32_t *clus, const int32_t *nclus, int64_t cap,
+nr::SharedArgs shared_args(const nr_index *ix, const nr_params *p, int P, const void *q,
+                           int64_t nq, int k, const uint32_t *clus, const int32_t *nclus, int64_t cap,
                            const Buffers &B, int64_t *out_ids, float *out_dists,
                            int32_t *qstats) {
   nr::SharedArgs a{};
@@ -653,7 +653,11 @@ nr::SharedArgs shared_args(const nr_index *ix, const nr_params *p, const void *q
   a.scan_head = scan_head(ix);
   a.scan_hb = (const unsigned char *)ix->d.rows;  // the head plane, or the rows themselves
   a.scan_hs = ix->d.head_bytes > 0 ? (uint64_t)ix->d.head_bytes : (uint64_t)a.row_bytes;
-  a.seed = nr::seed_rule(a.is_u8, a.row_bytes, k);
+  // rows of the mean list: the probes' buckets, the empty ones left out where
+  // the directory shows them
+  const double buckets = std::min(std::ldexp(1.0, ix->d.b), (double)ix->d.n_clusters);
+  const double list_rows = std::min((double)ix->d.n, P * ((double)ix->d.n / buckets));
+  a.seed = nr::seed_rule(a.is_u8, a.row_bytes, k, nq * list_rows * a.row_bytes);
   if (p->shared_seed_rows > 0) {
     a.seed.lo = p->shared_seed_rows > k ? (uint32_t)p->shared_seed_rows : (uint32_t)k;
     a.seed.div = a.seed.brief = 0;
@@ -1114,7 +1118,7 @@ nr_status nr_search_ex(const nr_index *cix, const void *queries, const float *lo
     nr::SharedArgs sa{};
     nr::PairHistArgs ph{};
     if (B.shared) {
-      sa = shared_args(ix, p, qp, n, k, B.clus, B.nclus, cap, B, out_ids + q0 * k,
+      sa = shared_args(ix, p, P, qp, n, k, B.clus, B.nclus, cap, B, out_ids + q0 * k,
                        out_dists + q0 * k, qs);
       ph = nr::pair_hist_args(sa);
       // pair counts start at zero: cleared in full only for a new

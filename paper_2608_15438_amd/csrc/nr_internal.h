@@ -29,17 +29,14 @@ constexpr int64_t ENCODE_ROWS = (int64_t)1 << 26;
 constexpr uint32_t OWN_TILE_MIN_ROWS = NR_OWN_TILE_MIN_ROWS;  // smallest tile of the own pass
 // Rows of a query's first clusters that it refines on its own before the
 // shared scan: about 1 / div of the rows its list holds (estimated from the
-// list's first clusters, which are its larger ones), within [lo, hi]; lists
-// estimated at most `brief` rows long take 2 lo, so that a batch of short
-// lists leaves the scan nothing (1M x 128, 725 rows a list: 0.78 ms, but 0.95
-// ms with the few lists past 1024 rows in the scan).  More seed rows give tighter bounds
-// (fewer survivors of the scan, and for uint8 rows fewer rows that pass the
-// head test) but are read once per query instead of once per batch, and the
-// rows that the bound acts on grow with the list.  fp32 heads drop few rows,
-// so fp32 seeds are the smaller; uint8 rows past 1 KB keep 1024.  The bound is
-// the seed's k-th key, so a large k needs SEED_ROWS_PER_K rows per neighbour:
-// with 8, the survivors of k = 64 flooded their lists.  Whole searches on
-// MI355X with seeds of 256 / 512 / 1024 / 2048 / 4096 rows, ms:
+// mean size of its first 64 clusters), within [lo, hi].  More seed rows give
+// tighter bounds (fewer survivors of the scan, and for uint8 rows fewer rows
+// that pass the head test) but are read once per query instead of once per
+// batch, and the rows that the bound acts on grow with the list.  fp32 heads
+// drop few rows, so fp32 seeds are the smaller; uint8 rows past 1 KB keep 1024.
+// The bound is the seed's k-th key, so a large k needs SEED_ROWS_PER_K rows per
+// neighbour: with 8, the survivors of k = 64 flooded their lists.  Whole searches
+// on MI355X with seeds of 256 / 512 / 1024 / 2048 / 4096 rows, ms:
 //   fp32, k = 10:   25M x 96 (11k rows a list) 3.62 / 3.51 / 3.65 / 4.2 / 4.89, 1M x 200 (9k)
 //                   2.07 / 2.15 / 2.39 / 2.98 / 4.10, 500k x 768 (9k) 14.8 / 3.26 / 3.00 /
 //                   3.68 / 5.46, 500k x 1536 (4k) 1.16 / 1.27 / 1.63 / - / -
@@ -47,13 +44,32 @@ constexpr uint32_t OWN_TILE_MIN_ROWS = NR_OWN_TILE_MIN_ROWS;  // smallest tile o
 //                   3.16 / 2.86 / 2.97 / 3.12, 256M x 128 (56k) 8.5 / 6.3 / 5.5 / 5.17 / 5.04
 //   k = 64:         1M x 100 fp32 2.91 / 2.01 / 1.96 / 2.15 / 2.65, 4M x 256 uint8 7.85 /
 //                   2.63 / 1.82 / 1.88 / 2.15, 500k x 1536 fp32 20 / 18 / 4.75 / 4.29 / 5.89
+// Short lists: a scan costs some 150 us however little it is left, so a batch of
+// short lists goes best without one.
+//   uint8: lists estimated at most `brief` rows long take 2 lo (1M x 128 in
+//   clusters of three, 725 rows a list: 0.78 ms, but 0.95 ms with the few lists
+//   past 1024 rows in the scan).
+//   fp32 rows of at most 1 KB: where the batch's lists (probe budget x mean
+//   bucket) come to at most SEED_WHOLE bytes, a query reads up to 4096 rows of
+//   its own.  Seeds of 512 / 4096 rows, 1M rows in 8192 buckets, us:
+//     d = 96:  3,000 queries of 1.0k rows (0.8 GB) 514 / 338, 1.5k (1.3 GB) 566 / 440, 2.7k
+//              (2.2 GB) 638 / 754; 10,000 of 1.0k (2.8 GB) 831 / 781, 1.5k (4.2 GB) 925 / 1087;
+//              700 of 1.5k (0.3 GB) 355 / 221, 5.3k (1.1 GB) 494 / 466
+//     d = 32:  3,000 of 1.4k (0.3 GB) 786 / 344, 5.2k (1.2 GB) 829 / 783; 10,000 of 1.4k
+//              (0.9 GB) 970 / 632, 2.7k (1.9 GB) 1026 / 1086
+//     d = 256: 512 of 1.3k (0.6 GB) 356 / 407, 2.8k (1.3 GB) 453 / 511; 3,000 of 0.9k (2.3 GB)
+//              619 / 630
+//   Longer rows gain nothing from it (500k x 768, 512 queries of 1.1k rows 542 / 688).
 struct SeedRule {
   uint32_t lo, hi, div, brief;  // div 0: lo rows whatever the list
 };
 constexpr uint32_t SEED_ROWS_PER_K = 32;
-inline SeedRule seed_rule(bool is_u8, int row_bytes, int k) {
+constexpr double SEED_WHOLE = 1.5e9;
+// list_bytes: the bytes of all lists' rows together, about
+inline SeedRule seed_rule(bool is_u8, int row_bytes, int k, double list_bytes) {
   SeedRule r = is_u8 ? (row_bytes > 1024 ? SeedRule{1024, 1024, 0, 0} : SeedRule{1024, 4096, 12, 8192})
-                     : SeedRule{512, 4096, 24, 2048};
+               : row_bytes <= 1024 && list_bytes <= SEED_WHOLE ? SeedRule{4096, 4096, 0, 0}
+                                                               : SeedRule{512, 4096, 24, 0};
   const uint32_t by_k = SEED_ROWS_PER_K * (uint32_t)k;
   if (r.lo < by_k) r.lo = by_k;
   if (r.hi < r.lo) r.hi = r.lo;

@@ -76,6 +76,19 @@ def test_shared_equals_per_query(dtype, d, head, n, b, nq, P, seed_rows):
     ix.close()
 
 
+@pytest.mark.parametrize("d,nq,P", [(24, 700, 3), (24, 3000, 60), (24, 3000, 90), (256, 1500, 4),
+                                    (260, 700, 4), (260, 700, 60)])
+def test_default_seeds_of_fp32_lists(d, nq, P):
+    # lists of 0.7k to 21k rows, batches on both sides of 1.5 GB, rows on both of 1 KB
+    from paper_2608_15438_amd import neuroute as NR
+    ix, rows = make_index(60_001, d, 8, NR.NR_F32, 64, seed=d)
+    g = torch.Generator(device="cuda").manual_seed(P)
+    q = rows[torch.randint(0, 60_001, (nq,), generator=g, device="cuda")].clone()
+    for k in (10, 64):
+        both(ix, q, k, P, 8)
+    ix.close()
+
+
 def test_shared_equals_per_query_large_scan():
     # more work (rows x groups of 8 queries) than 4 tiles of 4096 per wave
     from paper_2608_15438_amd import neuroute as NR
