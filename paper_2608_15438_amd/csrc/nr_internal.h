@@ -45,13 +45,12 @@ constexpr uint32_t OWN_TILE_MIN_ROWS = NR_OWN_TILE_MIN_ROWS;  // smallest tile o
 //   k = 64:         1M x 100 fp32 2.91 / 2.01 / 1.96 / 2.15 / 2.65, 4M x 256 uint8 7.85 /
 //                   2.63 / 1.82 / 1.88 / 2.15, 500k x 1536 fp32 20 / 18 / 4.75 / 4.29 / 5.89
 // Short lists: a scan costs some 150 us however little it is left, so a batch of
-// short lists goes best without one.
-//   uint8: lists estimated at most `brief` rows long take 2 lo (1M x 128 in
-//   clusters of three, 725 rows a list: 0.78 ms, but 0.95 ms with the few lists
-//   past 1024 rows in the scan).
-//   fp32 rows of at most 1 KB: where the batch's lists (probe budget x mean
-//   bucket) come to at most SEED_WHOLE bytes, a query reads up to 4096 rows of
-//   its own.  Seeds of 512 / 4096 rows, 1M rows in 8192 buckets, us:
+// short lists goes best without one.  Where the lists of rows of at most 1 KB
+// (probe budget x mean bucket) come to at most SEED_WHOLE bytes, a query reads up
+// to 4096 rows of its own; past that, uint8 lists estimated at most `brief` rows
+// long take 2 lo (1M x 128 in clusters of three, 725 rows a list: 0.78 ms, but 0.95
+// ms with the few lists past 1024 rows in the scan).  1M rows in 8192 buckets, us:
+//   fp32, seeds of 512 / 4096 rows:
 //     d = 96:  3,000 queries of 1.0k rows (0.8 GB) 514 / 338, 1.5k (1.3 GB) 566 / 440, 2.7k
 //              (2.2 GB) 638 / 754; 10,000 of 1.0k (2.8 GB) 831 / 781, 1.5k (4.2 GB) 925 / 1087;
 //              700 of 1.5k (0.3 GB) 355 / 221, 5.3k (1.1 GB) 494 / 466
@@ -59,6 +58,10 @@ constexpr uint32_t OWN_TILE_MIN_ROWS = NR_OWN_TILE_MIN_ROWS;  // smallest tile o
 //              (0.9 GB) 970 / 632, 2.7k (1.9 GB) 1026 / 1086
 //     d = 256: 512 of 1.3k (0.6 GB) 356 / 407, 2.8k (1.3 GB) 453 / 511; 3,000 of 0.9k (2.3 GB)
 //              619 / 630
+//   uint8, seeds by div and brief / of 4096 rows:
+//     d = 128: 10,000 of 2.7k (1.9 GB) 920 / 853, 4.7k (3.7 GB) 1044 / 1191; 1,000 of 9.7k
+//              (0.9 GB) 510 / 378, 19k (1.9 GB) 436 / 428
+//     d = 256: 512 of 7.1k (0.6 GB) 570 / 567; 700 of 12k (1.6 GB) 636 / 648
 //   Longer rows gain nothing from it (500k x 768, 512 queries of 1.1k rows 542 / 688).
 struct SeedRule {
   uint32_t lo, hi, div, brief;  // div 0: lo rows whatever the list
@@ -67,9 +70,9 @@ constexpr uint32_t SEED_ROWS_PER_K = 32;
 constexpr double SEED_WHOLE = 1.5e9;
 // list_bytes: the bytes of all lists' rows together, about
 inline SeedRule seed_rule(bool is_u8, int row_bytes, int k, double list_bytes) {
-  SeedRule r = is_u8 ? (row_bytes > 1024 ? SeedRule{1024, 1024, 0, 0} : SeedRule{1024, 4096, 12, 8192})
-               : row_bytes <= 1024 && list_bytes <= SEED_WHOLE ? SeedRule{4096, 4096, 0, 0}
-                                                               : SeedRule{512, 4096, 24, 0};
+  SeedRule r{512, 4096, 24, 0};
+  if (row_bytes <= 1024 && list_bytes <= SEED_WHOLE) r = SeedRule{4096, 4096, 0, 0};
+  else if (is_u8) r = row_bytes > 1024 ? SeedRule{1024, 1024, 0, 0} : SeedRule{1024, 4096, 12, 8192};
   const uint32_t by_k = SEED_ROWS_PER_K * (uint32_t)k;
   if (r.lo < by_k) r.lo = by_k;
   if (r.hi < r.lo) r.hi = r.lo;

@@ -76,12 +76,14 @@ def test_shared_equals_per_query(dtype, d, head, n, b, nq, P, seed_rows):
     ix.close()
 
 
-@pytest.mark.parametrize("d,nq,P", [(24, 700, 3), (24, 3000, 60), (24, 3000, 90), (256, 1500, 4),
-                                    (260, 700, 4), (260, 700, 60)])
-def test_default_seeds_of_fp32_lists(d, nq, P):
+@pytest.mark.parametrize("dtype,d,nq,P", [
+    ("f32", 24, 700, 3), ("f32", 24, 3000, 60), ("f32", 24, 3000, 90), ("f32", 256, 1500, 4),
+    ("f32", 260, 700, 4), ("f32", 260, 700, 60), ("u8", 64, 700, 12), ("u8", 64, 3000, 30),
+    ("u8", 64, 3000, 40), ("u8", 1024, 700, 4), ("u8", 1040, 700, 4)])
+def test_default_seeds(dtype, d, nq, P):
     # lists of 0.7k to 21k rows, batches on both sides of 1.5 GB, rows on both of 1 KB
     from paper_2608_15438_amd import neuroute as NR
-    ix, rows = make_index(60_001, d, 8, NR.NR_F32, 64, seed=d)
+    ix, rows = make_index(60_001, d, 8, NR.NR_F32 if dtype == "f32" else NR.NR_U8, 64, seed=d)
     g = torch.Generator(device="cuda").manual_seed(P)
     q = rows[torch.randint(0, 60_001, (nq,), generator=g, device="cuda")].clone()
     for k in (10, 64):
