@@ -146,7 +146,7 @@ typedef struct {
   int32_t refine_mode;   /* NR_REFINE_AUTO / _PER_QUERY / _SHARED (same results) */
   int32_t shared_seed_rows; /* shared schedule: rows of each list's leading clusters
                                kept for the query's own pass (>= k); 0: chosen
-                               per query from its list's rows and k */
+                               from the batch's and each list's rows and k */
   int32_t m_knots;
   float m_x[NR_MAX_KNOTS];
   float m_y[NR_MAX_KNOTS];

@@ -557,7 +557,10 @@ hipError_t run_refine(const nr_index *ix, const void *q, int64_t nq, int k, cons
   // with more, a tile's set-up and its partial list cost more than they gain.
   // Whole searches with tiles of at least 64 / 128 / 256 / 512 rows, us: one
   // query (756 rows, k = 10) 102 / 105 / 112 / 122; 48 (6,030 rows, k = 10) 127 / 120 / 113 /
-  // 115; 333 (3,700 rows, k = 33) 388 / 260 / 245 / 204
+  // 115; 333 (3,700 rows, k = 33) 388 / 260 / 245 / 204; 1M uint8 rows of 128, 2.6k rows a
+  // query: 8 queries 71 / 64 / 65 / 71, 24 81 / 71 / 68 / 74, 64 100 / 83 / 76 / 78, 150
+  // 144 / 111 / 87 / 86, 511 157 / 142 / 148 / 119.  Over twelve batches from 1 to 511 queries
+  // of 2k to 30k rows of 128 to 384 bytes the rule is within 10 % of the best of the four
   pa.tile_min = (uint32_t)std::min<int64_t>(nr::TILE_MIN_ROWS, std::max<int64_t>(64, 8 * nq));
   if (o.own_cseed) {
     pa.clus_out = B.clus_own;
@@ -1126,7 +1129,11 @@ nr_status nr_search_ex(const nr_index *cix, const void *queries, const float *lo
       HIP_OK(nr::launch_shared_hist(sa, w->clean_hist != B.hist, stream));
       w->clean_hist = nullptr;
     }
-    // refined query by query, a list's order is of no consequence
+    // refined query by query, a list's order does not change the result.  It does
+    // change when the slabs of fp32 rows past 1 KB stop, but the sort costs more:
+    // 500 queries, 200k x 1536 in 8 clusters per bucket, P = 48, 0.91 ms as scored
+    // and 1.10 sorted; the
+    // sort gains nothing in any of 90 such batches of 384 to 1536 dimensions
     HIP_OK(run_route(ix, lg, n, P, p, B, B.clus, B.nclus, cap, qs, stream,
                      B.shared ? &ph : nullptr, !B.shared));
     if (prof) HIP_OK(hipEventRecord(es.ev[3], stream));
