@@ -186,6 +186,15 @@ def _dev(t: torch.Tensor, name: str):
     return t
 
 
+def _scratch(n: int, dtype, device, stream=None):
+    """Work space of one call: the allocator hands it on only after `stream` is
+    done with it (it belongs to the current stream, the call's may be another)."""
+    t = torch.empty(n, dtype=dtype, device=device)
+    if stream is not None:
+        t.record_stream(stream)
+    return t
+
+
 def nr_stream_read(buf: torch.Tensor, sink: torch.Tensor, stream=None):
     """One streaming pass of 16-byte loads over a device tensor."""
     _dev(buf, "buf")
@@ -197,7 +206,7 @@ def nr_pair_sqdist(x: torch.Tensor, out: Optional[torch.Tensor] = None, stream=N
     """Squared distances [B, B] of the rows of x (fp32 [B, D], device)."""
     _dev(x, "x")
     B, D = x.shape
-    ws = torch.empty(int(lib().nr_pair_sqdist_ws(B, D)), dtype=torch.float32, device=x.device)
+    ws = _scratch(int(lib().nr_pair_sqdist_ws(B, D)), torch.float32, x.device, stream)
     if out is None:
         out = torch.empty((B, B), dtype=torch.float32, device=x.device)
     _check(lib().nr_pair_sqdist(_ptr(x), B, D, _ptr(ws), _ptr(out), _stream(stream)),
@@ -222,7 +231,7 @@ def nr_pair_quantile(d2_emb: torch.Tensor, q: float, limit: int = 1 << 24, out=N
     """fp64 [1] (device): the q-quantile of the first `limit` off-diagonal
     elements of the distances d2_emb [B, B]."""
     _dev(d2_emb, "d2_emb")
-    ws = torch.empty(int(lib().nr_pair_quantile_ws()), dtype=torch.uint8, device=d2_emb.device)
+    ws = _scratch(int(lib().nr_pair_quantile_ws()), torch.uint8, d2_emb.device, stream)
     if out is None:
         out = torch.empty(1, dtype=torch.float64, device=d2_emb.device)
     _check(lib().nr_pair_quantile(_ptr(d2_emb), d2_emb.shape[0], limit, float(q), _ptr(ws),

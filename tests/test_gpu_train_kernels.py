@@ -143,3 +143,27 @@ def test_pair_quantile_nan(at, limit):
     for q in (0.0, 0.005, 1.0):
         got, want = float(NR.nr_pair_quantile(d2, q, limit)), float(torch.quantile(off, q))
         assert got == want or (math.isnan(got) and math.isnan(want)), (q, got, want)
+
+
+def test_work_space_of_another_stream():
+    # the call's work space is freed when it returns: what the current stream
+    # allocates next must not land in it while the other stream still waits
+    g = torch.Generator(device="cuda").manual_seed(6)
+    x = torch.randn((1500, 64), generator=g, device="cuda")
+    want = NR.nr_pair_sqdist(x)
+    q = NR.nr_pair_quantile(want, 0.005)
+    side = torch.cuda.Stream()
+    d2, out = torch.empty_like(want), torch.empty_like(q)
+    for _ in range(3):
+        d2.zero_()
+        out.zero_()
+        torch.cuda.synchronize()
+        with torch.cuda.stream(side):
+            torch.cuda._sleep(20_000_000)
+        NR.nr_pair_sqdist(x, out=d2, stream=side)
+        NR.nr_pair_quantile(d2, 0.005, out=out, stream=side)
+        junk = [torch.full((n,), 1e9, device="cuda") for n in (1 << 13, 1 << 14, 1 << 16, 1 << 17, 1 << 18)]
+        torch.cuda.synchronize()
+        del junk
+        assert torch.equal(d2, want)
+        assert torch.equal(out, q)
