@@ -186,6 +186,14 @@ def _dev(t: torch.Tensor, name: str):
     return t
 
 
+def _fits(t: torch.Tensor, name: str, dtype, *shape):
+    """A device tensor of this dtype and shape (a count: at least that many elements)."""
+    _dev(t, name)
+    if t.dtype != dtype or (t.numel() < shape[0] if len(shape) == 1 else tuple(t.shape) != shape):
+        raise ValueError(f"{name} must be {dtype} {list(shape)}, got {t.dtype} {list(t.shape)}")
+    return t
+
+
 def _scratch(n: int, dtype, device, stream=None):
     """Work space of one call: the allocator hands it on only after `stream` is
     done with it (it belongs to the current stream, the call's may be another)."""
@@ -230,11 +238,14 @@ def nr_lsim_grad(d2_emb: torch.Tensor, lat: torch.Tensor, gamma_rho: float, tau_
 def nr_pair_quantile(d2_emb: torch.Tensor, q: float, limit: int = 1 << 24, out=None, stream=None):
     """fp64 [1] (device): the q-quantile of the first `limit` off-diagonal
     elements of the distances d2_emb [B, B]."""
-    _dev(d2_emb, "d2_emb")
+    B = d2_emb.shape[0]
+    _fits(d2_emb, "d2_emb", torch.float32, B, B)
+    if out is not None:
+        _fits(out, "out", torch.float64, 1)
     ws = _scratch(int(lib().nr_pair_quantile_ws()), torch.uint8, d2_emb.device, stream)
     if out is None:
         out = torch.empty(1, dtype=torch.float64, device=d2_emb.device)
-    _check(lib().nr_pair_quantile(_ptr(d2_emb), d2_emb.shape[0], limit, float(q), _ptr(ws),
+    _check(lib().nr_pair_quantile(_ptr(d2_emb), B, limit, float(q), _ptr(ws),
                                   _ptr(out), _stream(stream)), "nr_pair_quantile")
     return out
 
@@ -243,9 +254,10 @@ def nr_lsim_grad_at(d2_emb: torch.Tensor, lat: torch.Tensor, gamma_rho: float,
                     stats: torch.Tensor, stream=None):
     """nr_lsim_grad with tau_emb = sqrt(stats[2]) read on the device; (sum, count)
     go to stats[:2] (fp64 [3]).  Returns grad_lat fp32 [B, L]."""
-    _dev(d2_emb, "d2_emb")
-    _dev(lat, "lat")
     B, L = lat.shape
+    _fits(d2_emb, "d2_emb", torch.float32, B, B)
+    _fits(lat, "lat", torch.float32, B, L)
+    _fits(stats, "stats", torch.float64, 3)
     grad = torch.empty((B, L), dtype=torch.float32, device=lat.device)
     _check(lib().nr_lsim_grad_at(_ptr(d2_emb), _ptr(lat), B, L, float(gamma_rho),
                                  C.c_void_p(stats.data_ptr() + 16), _ptr(stats), _ptr(grad),

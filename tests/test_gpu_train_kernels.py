@@ -167,3 +167,17 @@ def test_work_space_of_another_stream():
         del junk
         assert torch.equal(d2, want)
         assert torch.equal(out, q)
+
+
+def test_wrong_tensors_are_refused():
+    # the kernels read and write by the shapes of one argument
+    d2, lat = torch.rand((8, 8), device="cuda"), torch.rand((8, 3), device="cuda")
+    stats = torch.ones(3, dtype=torch.float64, device="cuda")
+    NR.nr_lsim_grad_at(d2, lat, 0.5, stats)
+    for a in ((d2, lat, stats.float()), (d2, lat, stats[:2]), (d2[:7], lat, stats),
+              (d2, lat.double(), stats), (d2, lat[:7].contiguous(), stats), (d2, lat, stats.cpu())):
+        with pytest.raises(ValueError):
+            NR.nr_lsim_grad_at(a[0], a[1], 0.5, a[2])
+    for a in ((d2.double(), None), (d2[:5], None), (d2, stats.float()), (d2, stats[:0])):
+        with pytest.raises(ValueError):
+            NR.nr_pair_quantile(a[0], 0.5, out=a[1])
