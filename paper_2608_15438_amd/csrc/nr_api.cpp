@@ -1132,8 +1132,8 @@ nr_status nr_search_ex(const nr_index *cix, const void *queries, const float *lo
     // refined query by query, a list's order does not change the result.  It does
     // change when the slabs of fp32 rows past 1 KB stop, but the sort costs more:
     // 500 queries, 200k x 1536 in 8 clusters per bucket, P = 48, 0.91 ms as scored
-    // and 1.10 sorted; the
-    // sort gains nothing in any of 90 such batches of 384 to 1536 dimensions
+    // and 1.10 sorted; the sort gains nothing in any of 90 such batches of 384 to
+    // 1536 dimensions
     HIP_OK(run_route(ix, lg, n, P, p, B, B.clus, B.nclus, cap, qs, stream,
                      B.shared ? &ph : nullptr, !B.shared));
     if (prof) HIP_OK(hipEventRecord(es.ev[3], stream));
