@@ -12,9 +12,9 @@
 // are centred on the batch mean first (distances do not change), which keeps
 // the norms, and so the cancellation in the expansion, small; k_center writes
 // them in rows of whole 64-byte groups, so the tiles load 16 bytes at a time
-// without bounds checks.  Sums, norms and dot products are fp32 chains in a
-// fixed order (rows of a block, blocks, dimensions), because pairs at the
-// mask's thresholds come in or drop out on one ulp and trained weights follow.
+// without bounds checks.  Norms and the expansion are taken in fp64: what
+// rounds is the fp32 chain of the dot products, two chains of every other
+// K-tile.
 //
 // k_pair_quantile: an order statistic of the off-diagonal distances (tau_emb
 // of a batch) by radix select over their bits.
@@ -30,8 +30,6 @@
 // the gradient is the same bit for bit on every run.  Only the numerator's
 // block sums meet in a double-precision atomic (its last bits may vary; the
 // mask count is exact).
-#include <algorithm>
-
 #include "nr_internal.h"
 
 namespace nr {
@@ -40,67 +38,92 @@ typedef float v4f_l __attribute__((ext_vector_type(4)));
 
 constexpr int LS_M = 64, LS_K = 16;
 
-// Column sums of x over blocks of LS_ROWS rows (partial[blk][c]), then the
-// column means (the partials added in block order).  A column's sum is one
-// chain over the block's rows, so its loads go out 64 at a time (4096 x 128 rows:
-// 62 us one after the other, 12 us so).
-constexpr int LS_ROWS = 256;
+// Column sums of x over blocks of LS_ROWS rows (partial[blk][c]) and the
+// column's range inside each block (range[blk][c]), then the shifts of the
+// columns from the partials, added in block order.  4096 x 128 rows: 62 us
+// with 256 rows per block (16 blocks, one long chain each), 4 us with 32.
+constexpr int LS_ROWS = 32;
 
-__global__ void __launch_bounds__(64) k_col_partial(const float *x, int64_t B, int D,
-                                                    float *partial) {
+__global__ void __launch_bounds__(128) k_col_partial(const float *x, int64_t B, int D,
+                                                     float *partial, float *range) {
   const int64_t r0 = (int64_t)blockIdx.x * LS_ROWS;
   const int nr = (int)(B - r0 < LS_ROWS ? B - r0 : LS_ROWS);
-  for (int64_t c = blockIdx.y * 64 + threadIdx.x; c < D; c += gridDim.y * 64) {
-    const float *col = x + r0 * D + c;
-    float s = 0.0f;
-    for (int i0 = 0; i0 < nr; i0 += 64) {
-      float v[64];
-#pragma unroll
-      for (int u = 0; u < 64; ++u) v[u] = i0 + u < nr ? col[(int64_t)(i0 + u) * D] : 0.0f;
-#pragma unroll
-      for (int u = 0; u < 64; ++u) s += v[u];
+  for (int c = threadIdx.x; c < D; c += 128) {
+    float s = 0.0f, lo = INFINITY, hi = -INFINITY;
+#pragma unroll 8
+    for (int i = 0; i < nr; ++i) {
+      const float v = x[(r0 + i) * D + c];
+      s += v;
+      lo = fminf(lo, v);
+      hi = fmaxf(hi, v);
     }
     partial[(int64_t)blockIdx.x * D + c] = s;
+    range[(int64_t)blockIdx.x * D + c] = hi - lo;
   }
 }
 
-__global__ void __launch_bounds__(64) k_col_mean(const float *partial, int64_t nblk, int64_t B,
-                                                 int D, float *mean) {
-  const int c = blockIdx.x * 64 + threadIdx.x;
-  if (c >= D) return;
+// The shift of a column: its mean, cut to 12 bits where that costs nothing.  Cut,
+// it leaves the rows up to 2^-11 of the mean off centre, against which the
+// products cancel (at a mean of 1e5 times the spread the distances were off by 2e-4
+// of their scale).  So it is cut only where that is at most 1/64 of the column's
+// range in every whole block of 32 rows, about 1/16 of the spread, less than half
+// a percent of the norms.  The distances' error is the same then (3.5e-8 of their
+// norm for 4096 uint8 rows of 128 either way, 1.3e-7 with fp32 norms and one
+// chain), and the bits stay what they were, which decide the pairs at the mask's
+// thresholds and so the trained weights.
+// Two waves per 64 columns: sums, ranges; sixteen loads of each in flight.
+__global__ void __launch_bounds__(128) k_col_mean(const float *partial, const float *range,
+                                                  int64_t nblk, int64_t B, int D, float *mean) {
+  __shared__ float s_least[64];
+  const int lane = lane_id();
+  const bool sums = threadIdx.x < WAVE;
+  const int64_t c = (int64_t)blockIdx.x * 64 + lane;
+  const int64_t n = sums || B < LS_ROWS ? nblk : B / LS_ROWS;   // ranges: of whole blocks
+  const float *col = (sums ? partial : range) + (c < D ? c : D - 1);
   double s = 0.0;
-#pragma unroll 16
-  for (int64_t b = 0; b < nblk; ++b) s += partial[b * D + c];
-  mean[c] = (float)(s / (double)B);
+  float least = INFINITY;
+  for (int64_t b0 = 0; b0 < n; b0 += 16) {
+    float v[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) v[u] = col[(b0 + u < n ? b0 + u : n - 1) * D];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+      s += b0 + u < n ? v[u] : 0.0f;
+      least = fminf(least, v[u]);
+    }
+  }
+  if (!sums) s_least[lane] = least;
+  __syncthreads();
+  if (!sums || c >= D) return;
+  const float m = (float)(s / (double)B);
+  const float cut = __uint_as_float(__float_as_uint(m) & 0xfffff000u);
+  mean[c] = 64.0f * fabsf(m - cut) <= s_least[lane] ? cut : m;
 }
 
-// centred rows xc [B][DP], zeros from D on, and their squared norms (one chain
-// over the dimensions in order); one wave per row
+// centred rows xc [B][DP], zeros from D on, and their squared norms; one wave
+// per row
 __global__ void __launch_bounds__(256) k_center(const float *x, int64_t B, int D, int DP,
-                                                const float *mean, float *xc, float *norm) {
+                                                const float *mean, float *xc, double *norm) {
   const int lane = lane_id();
   const int64_t i = (int64_t)blockIdx.x * 4 + threadIdx.x / WAVE;
   if (i >= B) return;
-  float s = 0.0f;
-  for (int c0 = 0; c0 < DP; c0 += WAVE) {
-    const int c = c0 + lane;
+  double s = 0.0;
+  for (int c = lane; c < DP; c += WAVE) {
     const float v = c < D ? x[i * D + c] - mean[c] : 0.0f;
-    if (c < DP) xc[i * DP + c] = v;
-#pragma unroll
-    for (int u = 0; u < WAVE; ++u) {   // zeros from D on leave the sum as it is
-      const float t = bcast_f32(v, u);
-      s = fmaf(t, t, s);
-    }
+    xc[i * DP + c] = v;
+    s += (double)v * (double)v;
   }
+  for (int m = 1; m < WAVE; m <<= 1) s += __shfl_xor(s, m);
   if (lane == 0) norm[i] = s;
 }
 
 // Tiles on and above the diagonal only; each writes its mirror too, so the
 // matrix is symmetric bit for bit.  The next K-tile is loaded while this one
 // is multiplied (two LDS buffers).  4096 rows of 128: 69 us with element-wise
-// loads and stores of the mirror, 39 us with 16-byte ones.
+// loads and stores of the mirror, 42 us with 16-byte ones and fp64 norms (which
+// bring the distances' error against 64 bits from 4.7e-7 to 1.8e-7).
 __global__ void __launch_bounds__(256) k_pair_sqdist(const float *xc, int64_t B, int DP,
-                                                      const float *norm, float *out, int vec) {
+                                                      const double *norm, float *out, int vec) {
   __shared__ float As[2][LS_K][LS_M + 4];
   __shared__ float Bs[2][LS_K][LS_M + 4];
   const int tid = threadIdx.x;
@@ -113,9 +136,10 @@ __global__ void __launch_bounds__(256) k_pair_sqdist(const float *xc, int64_t B,
   const uint32_t bi = t - (uint32_t)((uint64_t)bj * (bj + 1) / 2);
   const int64_t i0 = (int64_t)bi * LS_M, j0 = (int64_t)bj * LS_M;
   const int wm = (wave & 1) * 32, wn = (wave >> 1) * 32;
-  v4f_l acc[2][2];
-  for (int i = 0; i < 2; ++i)
-    for (int j = 0; j < 2; ++j) acc[i][j] = v4f_l{0.f, 0.f, 0.f, 0.f};
+  v4f_l acc[2][2][2];   // [K-tile parity]
+  for (int p = 0; p < 2; ++p)
+    for (int i = 0; i < 2; ++i)
+      for (int j = 0; j < 2; ++j) acc[p][i][j] = v4f_l{0.f, 0.f, 0.f, 0.f};
   // thread -> row tid / 4, four columns from 4 (tid % 4) (rows past B repeat
   // the last one and are not written)
   const int lr = tid >> 2, lk = (tid & 3) * 4;
@@ -152,7 +176,8 @@ __global__ void __launch_bounds__(256) k_pair_sqdist(const float *xc, int64_t B,
       for (int i = 0; i < 2; ++i)
 #pragma unroll
         for (int j = 0; j < 2; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[i], bv[j], acc[i][j], 0, 0, 0);
+          acc[buf][i][j] =
+              __builtin_amdgcn_mfma_f32_16x16x4f32(av[i], bv[j], acc[buf][i][j], 0, 0, 0);
     }
     if (more) stash(buf ^ 1);
     __syncthreads();
@@ -169,12 +194,13 @@ __global__ void __launch_bounds__(256) k_pair_sqdist(const float *xc, int64_t B,
       const int64_t cj = j0 + wn + 16 * j + (lane & 15);
       const int64_t r0 = i0 + wm + 16 * i + 4 * (lane >> 4);
       if (cj >= B) continue;
-      const float nj = norm[cj];
+      const double nj = norm[cj];
       float v[4];
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         const int64_t ri = r0 + r;
-        v[r] = (norm[ri < B ? ri : B - 1] + nj) - 2.0f * acc[i][j][r];
+        const double ni = norm[ri < B ? ri : B - 1];
+        v[r] = (float)((ni + nj) - 2.0 * ((double)acc[0][i][j][r] + (double)acc[1][i][j][r]));
         v[r] = v[r] > 0.f ? v[r] : 0.f;
         if (ri == cj) v[r] = 0.f;
         if (ri < B) out[ri * B + cj] = v[r];
@@ -491,7 +517,7 @@ __global__ void __launch_bounds__(64 * LG_WAVES) k_lsim_grad(const float *d2, co
       }
     }
   }
-  // the gradient: a wave's four subsets, then the waves, in pairs
+  // the gradient: a wave's four subsets, then the waves, in a fixed order
   __syncthreads();
   float *gs = li_s;   // [wave][column][L]
 #pragma unroll
@@ -511,15 +537,10 @@ __global__ void __launch_bounds__(64 * LG_WAVES) k_lsim_grad(const float *d2, co
   }
   __syncthreads();
   for (int e = tid; e < LG_COLS * L; e += 64 * LG_WAVES) {
-    float v[LG_WAVES];
-#pragma unroll
-    for (int k = 0; k < LG_WAVES; ++k) v[k] = gs[k * LG_COLS * L + e];
-#pragma unroll
-    for (int d = 1; d < LG_WAVES; d <<= 1)
-#pragma unroll
-      for (int k = 0; k < LG_WAVES; k += 2 * d) v[k] += v[k + d];
+    float v = 0.f;
+    for (int k = 0; k < LG_WAVES; ++k) v += gs[k * LG_COLS * L + e];
     const int64_t jj = (int64_t)blockIdx.x * LG_COLS + e / L;
-    if (jj < B) grad[jj * L + e % L] = v[0];
+    if (jj < B) grad[jj * L + e % L] = v;
   }
   if (tid == 0) {
     double tn = 0.0, tc = 0.0;
@@ -535,9 +556,9 @@ __global__ void __launch_bounds__(64 * LG_WAVES) k_lsim_grad(const float *d2, co
 static int center_stride(int D) { return (D + LS_K - 1) / LS_K * LS_K; }
 
 size_t pair_sqdist_ws_floats(int64_t B, int D) {
-  // the centred rows from a 16-byte boundary on, then partial sums, means, norms
+  // the centred rows from a 16-byte boundary on, then norms, partial sums, ranges, means
   return 4 + (size_t)B * center_stride(D) +
-         (size_t)((B + LS_ROWS - 1) / LS_ROWS + 1) * (size_t)D + (size_t)B;
+         (size_t)(2 * ((B + LS_ROWS - 1) / LS_ROWS) + 1) * (size_t)D + 2 * (size_t)B;
 }
 
 hipError_t launch_pair_sqdist(const float *x, int64_t B, int D, float *ws, float *out,
@@ -546,11 +567,12 @@ hipError_t launch_pair_sqdist(const float *x, int64_t B, int D, float *ws, float
   const int64_t nblk = (B + LS_ROWS - 1) / LS_ROWS;
   const int DP = center_stride(D);
   float *xc = reinterpret_cast<float *>((reinterpret_cast<uintptr_t>(ws) + 15) & ~(uintptr_t)15);
-  float *norm = xc + B * DP, *partial = norm + B, *mean = partial + nblk * D;
-  hipLaunchKernelGGL(k_col_partial, dim3((unsigned)nblk, (unsigned)std::min((D + 63) / 64, 65535)),
-                     dim3(64), 0, s, x, B, D, partial);
-  hipLaunchKernelGGL(k_col_mean, dim3((unsigned)((D + 63) / 64)), dim3(64), 0, s, partial, nblk, B,
-                     D, mean);
+  double *norm = reinterpret_cast<double *>(xc + B * DP);   // DP: whole 64-byte groups
+  float *partial = reinterpret_cast<float *>(norm + B), *range = partial + nblk * D;
+  float *mean = range + nblk * D;
+  hipLaunchKernelGGL(k_col_partial, dim3((unsigned)nblk), dim3(128), 0, s, x, B, D, partial, range);
+  hipLaunchKernelGGL(k_col_mean, dim3((unsigned)((D + 63) / 64)), dim3(128), 0, s, partial, range,
+                     nblk, B, D, mean);
   hipLaunchKernelGGL(k_center, dim3((unsigned)((B + 3) / 4)), dim3(256), 0, s, x, B, D, DP, mean,
                      xc, norm);
   const int64_t gb = (B + LS_M - 1) / LS_M;
