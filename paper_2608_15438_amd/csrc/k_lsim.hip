@@ -120,8 +120,9 @@ __global__ void __launch_bounds__(256) k_center(const float *x, int64_t B, int D
 // Tiles on and above the diagonal only; each writes its mirror too, so the
 // matrix is symmetric bit for bit.  The next K-tile is loaded while this one
 // is multiplied (two LDS buffers).  4096 rows of 128: 69 us with element-wise
-// loads and stores of the mirror, 42 us with 16-byte ones and fp64 norms (which
-// bring the distances' error against 64 bits from 4.7e-7 to 1.8e-7).
+// loads and stores of the mirror, 43 us with 16-byte ones and two chains (which
+// with fp64 norms bring the distances' error against 64 bits from 1.3e-7 of
+// their norm to 3.5e-8; 39 us with one chain).
 __global__ void __launch_bounds__(256) k_pair_sqdist(const float *xc, int64_t B, int DP,
                                                       const double *norm, float *out, int vec) {
   __shared__ float As[2][LS_K][LS_M + 4];
